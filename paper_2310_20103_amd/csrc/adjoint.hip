@@ -283,6 +283,7 @@ __global__ void combine_adj_kernel(PairGeom g, int nb, int splitk, const double*
     const int v = (int)i / g.nc, c = (int)i - v * g.nc;  // (N_v N_c < 2^31)
     const long off = (long)v * g.ncp + c;
     double y = 0.0;
+#pragma unroll 4
     for (int s = 0; s < splitk; ++s) y += yb[s * stride_s + off];
     const long o = (long)b * g.nvc + i;
     const double x = sj[o];

@@ -204,6 +204,7 @@ struct gwl_ctx {
   // c >= N_c, r >= N_r) are written once at allocation and must never hold
   // the other precision's bytes.
   DevBuf<double> u64;          // [cap][NVp][NCp]
+  DevBuf<double> u64c;         // [cap][N_v N_c] operand of the pair-density GEMMs
   DevBuf<f16_t> u16;           // [cap][NVp][NCp] FP16, scaled by u_scale
   DevBuf<unsigned char> rho;   // [nvt][cap][NRp] x 8 (fully written by the first GEMM)
   DevBuf<double> vpot64;       // [cap][NRp]
@@ -320,6 +321,19 @@ struct gwl_ctx {
     return g;
   }
 
+  // FP64 products of nb vectors on the pair-density GEMMs (compact operands)?
+  bool pd(int nb) const { return fp64_kernel == 1 && gemm_pd_wins(kd(), nb); }
+  // the geometry and buffer of the FP64 operands of nb vectors' K product
+  PairGeom geom64(int nb, bool a_op = false) const {
+    PairGeom g = pair_geom(a_op);
+    if (pd(nb)) {
+      g.nvp = nv;
+      g.ncp = nc;
+    }
+    return g;
+  }
+  double* ubuf64(int nb) const { return pd(nb) ? u64c.p : u64.p; }
+
   int nvt_max() const {
     return std::max(std::max(gemm1_f64_vtiles(gd), gemm1_f16s_vtiles(gd)),
                     std::max(gemm1_f64m_vtiles(gd), gemm1_f16_vtiles(gd)));
@@ -330,11 +344,13 @@ struct gwl_ctx {
   // K range of at least 2048 grid points.
   int auto_splitk(int nb, int prec) const {
     if (splitk > 0) return splitk;
+    if (prec == GWL_FP64 && pd(nb)) return gemm2_pd_split(kd(), nb);  // (not tuned)
     if (tuned[prec].B == nb && tuned[prec].S > 0) return tuned[prec].S;
     return heuristic_splitk(nb, prec);
   }
   int heuristic_splitk(int nb, int prec) const {
     const GemmDims& d = kd();
+    if (prec == GWL_FP64 && pd(nb)) return gemm2_pd_split(d, nb);
     long blocks;
     if (!fp64_kernel)
       blocks = (long)nb * (d.nvp / 64) * ceil_div(d.ncp, 64);
@@ -358,6 +374,7 @@ struct gwl_ctx {
       ta.ensure((size_t)nb * nvc);
       tb.ensure((size_t)nb * nvc);
       u64.ensure((size_t)nb * nvpc);
+      u64c.ensure(gemm_pd_u_size(nb, nvc));
       u16.ensure((size_t)alloc_rows_u(nb, gd.nvp) * gd.ncp);
       rho.ensure((size_t)nvt_max() * nb * gd.nrp * 8);
       vpot64.ensure((size_t)nb * gd.nrp);
@@ -408,8 +425,12 @@ struct gwl_ctx {
     if (prec == GWL_FP64) {
       const double* crc = is ? ipsi_c_rc64.p : psi_c_rc64.p;
       const double* vrv = is ? ipsi_v_rv64.p : psi_v_rv64.p;
+      const double* pt = is ? ipsi_t.p : psi_t.p;
       double* rp = reinterpret_cast<double*>(rho.p);
-      if (fp64_kernel) {
+      if (pd(nb)) {
+        gemm1_pd(d, nb, pt, pt + (size_t)d.nvp * d.nrp, u64c.p, rp, st);
+        nvt = 1;
+      } else if (fp64_kernel) {
         gemm1_f64m(d, nb, crc, vrv, u64.p, rp, st);
         nvt = gemm1_f64m_vtiles(d);
       } else {
@@ -460,10 +481,7 @@ struct gwl_ctx {
       const double* pv = pt;
       const double* pc = pt + (size_t)d.nvp * d.nrp;
       prof_begin();
-      if (fp64_kernel)
-        gemm2_f64m(d, nb, S, pv, pc, vp, yp, st);
-      else
-        gemm2_f64(d, nb, S, pv, pc, vp, yp, st);
+      second_gemm64(d, nb, S, pv, pc, vp, yp);
       prof_end(1, nb);
     } else {
       float* rp = reinterpret_cast<float*>(rho.p);
@@ -490,6 +508,16 @@ struct gwl_ctx {
     }
   }
 
+  void second_gemm64(const GemmDims& d, int nb, int S, const double* pv, const double* pc,
+                     const double* v, double* y) {
+    if (pd(nb))
+      gemm2_pd(d, nb, S, pv, pc, v, y, stream);
+    else if (fp64_kernel)
+      gemm2_f64m(d, nb, S, pv, pc, v, y, stream);
+    else
+      gemm2_f64(d, nb, S, pv, pc, v, y, stream);
+  }
+
   // vout [nb][N_rp] <- Hartree potentials of the densities rho_b(r) =
   // sum_vc phi_v(r) phi_c(r) u_b[v][c] of the FP64 operands already in u64
   // (the first half of the K product, on the grid).
@@ -509,10 +537,10 @@ struct gwl_ctx {
   }
 
   void cast(int nb, const double* x, int prec, bool a_op = false) {
-    PairGeom g = pair_geom(a_op);
     if (prec == GWL_FP64) {
-      cast_u<double>(g, nb, x, nvc, u64.p, stream);
+      cast_u<double>(geom64(nb, a_op), nb, x, nvc, ubuf64(nb), stream);
     } else {
+      PairGeom g = pair_geom(a_op);
       g.uscale = u_scale;
       cast_u<f16_t>(g, nb, x, nvc, u16.p, stream);
     }
@@ -520,12 +548,12 @@ struct gwl_ctx {
 
   void do_combine(int nb, int S, int prec, const double* x, const double* tp, double* out,
                   double* acc, int mode, double c0, double cj, bool write_u) {
-    PairGeom g = pair_geom(mode == 3);
     if (prec == GWL_FP64)
-      combine<double, double>(g, nb, S, reinterpret_cast<const double*>(ypart.p), x, tp, out,
-                              acc, mode, poly_lo, poly_hi, c0, cj,
-                              write_u ? u64.p : nullptr, stream);
+      combine<double, double>(geom64(nb, mode == 3), nb, S,
+                              reinterpret_cast<const double*>(ypart.p), x, tp, out, acc, mode,
+                              poly_lo, poly_hi, c0, cj, write_u ? ubuf64(nb) : nullptr, stream);
     else {
+      PairGeom g = pair_geom(mode == 3);
       g.uscale = u_scale;
       // first GEMM: u and both orbital factors scaled; second GEMM: phi_v and
       // phi_c scaled again, and s_b per row (g.vmax)
@@ -600,14 +628,13 @@ struct gwl_ctx {
     pair_product(psi_t.p, gd.nrp, (int)nr, mrow, nrow, cnt, rp, stream);
     poisson_launch<double>(pg64, rp, gd.nrp, 0, 1, vp, gd.nrp, cnt,
                            reinterpret_cast<cplx<double>*>(fftx.p), stream);
-    const int S = auto_splitk(cnt, GWL_FP64);
+    // (the coupling integrals stay on the grid when the K product is on the points)
+    const int S = isdf_on && !splitk && pd(cnt) ? gemm2_pd_split(gd, cnt)
+                                                : auto_splitk(cnt, GWL_FP64);
     const double* pv = psi_t.p;
     const double* pc = psi_t.p + (size_t)gd.nvp * gd.nrp;
-    if (fp64_kernel)
-      gemm2_f64m(gd, cnt, S, pv, pc, vp, yp, stream);
-    else
-      gemm2_f64(gd, cnt, S, pv, pc, vp, yp, stream);
-    coupling_finish<double>(pair_geom(tda != 0), cnt, S, yp, dst, ldp, stream);
+    second_gemm64(gd, cnt, S, pv, pc, vp, yp);
+    coupling_finish<double>(geom64(cnt, tda != 0), cnt, S, yp, dst, ldp, stream);
   }
 
   // w = p_g(C) q over nb slots; replays a captured graph of the whole product
@@ -735,8 +762,10 @@ struct gwl_ctx {
           if (B > bmax && B != cands[0]) break;
           ensure_work(B, 1, false);
           const int s0 = heuristic_splitk(B, prec);
+          const bool flat = prec == GWL_FP64 && pd(B);  // (has its own split rule)
           for (int S : {s0 / 2, s0, s0 * 2}) {
-            if (S < 1 || S > 32 || (S > 1 && (long)kd().nrp / S < 1024)) continue;
+            if (flat && S != s0) continue;
+            if (!flat && (S < 1 || S > 32 || (S > 1 && (long)kd().nrp / S < 1024))) continue;
             cast(B, q.p, prec);
             k_product(B, prec, S);  // warm
             GWL_HIP(hipEventRecord(e0, stream));

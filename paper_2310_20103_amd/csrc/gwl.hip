@@ -621,11 +621,9 @@ gwl_status gwl_potential_product(gwl_ctx* ctx, const double* v, double* y, int n
         const double* pv = c.psi_t.p;
         const double* pc = c.psi_t.p + (size_t)d.nvp * d.nrp;
         double* yp = reinterpret_cast<double*>(c.ypart.p);
-        if (c.fp64_kernel)
-          gemm2_f64m(d, nb, S, pv, pc, c.vpot64.p, yp, st);
-        else
-          gemm2_f64(d, nb, S, pv, pc, c.vpot64.p, yp, st);
-        potprod_finish_kernel<double><<<gy, 256, 0, st>>>(c.nv, c.nc, d.nvp, d.ncp, nb, S, yp,
+        c.second_gemm64(d, nb, S, pv, pc, c.vpot64.p, yp);
+        const PairGeom g = c.geom64(nb);
+        potprod_finish_kernel<double><<<gy, 256, 0, st>>>(c.nv, c.nc, g.nvp, g.ncp, nb, S, yp,
                                                           nullptr, c.dv, yb);
       } else {
         pot16_exp_kernel<<<nb, 256, 0, st>>>(vb, c.nr, c.pv16_exp, c.vexp32.p);

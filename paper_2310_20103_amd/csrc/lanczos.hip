@@ -103,6 +103,7 @@ __device__ inline void combine_pairs(const PairGeom& g, int b, long stride_s, co
     const int v = i / g.nc, c = i - v * g.nc;  // c even: both elements in row v
     const long off = (long)v * g.ncp + c;
     double y0 = 0.0, y1 = 0.0;
+#pragma unroll 4
     for (int s = 0; s < splitk; ++s) {
       const typename Two<Y>::T t = *reinterpret_cast<const typename Two<Y>::T*>(yb + s * stride_s + off);
       y0 += (double)t.x;
@@ -171,6 +172,7 @@ __global__ void combine_kernel(PairGeom g, int nb, int splitk, const Y* __restri
     const int v = (int)i / g.nc, c = (int)i - v * g.nc;  // (N_v N_c < 2^31)
     const long off = (long)v * g.ncp + c;
     double y = 0.0;
+#pragma unroll 4
     for (int s = 0; s < splitk; ++s) y += (double)yb[s * stride_s + off];
     y *= ysc;
     const double xi = xb[i];
@@ -210,6 +212,7 @@ __global__ void coupling_finish_kernel(PairGeom g, int cnt, int splitk, const Y*
     const int v = (int)e / g.nc, c = (int)e - v * g.nc;  // (N_v N_c < 2^31)
     const long off = (long)v * g.ncp + c;
     double y = 0.0;
+#pragma unroll 4
     for (int s = 0; s < splitk; ++s) y += (double)yb[s * stride_s + off];
     // P_nm = (nm|vc) Delta^1/2, or (nm|vc) itself for Tamm-Dancoff
     p[(long)i * ldp + e] = g.tda ? g.dv * y : g.dv * g.sdelta[e] * y;

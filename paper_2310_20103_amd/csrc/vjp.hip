@@ -120,7 +120,9 @@ gwl_status vjp_run(gwl_ctx* ctx, VjpMode mode, const int* qp_states, int n_qp, i
     // (the recompute must repeat the forward's arithmetic exactly)
     GWL_CHECK(!bwd_only || (B == sv->B && S == sv->S), GWL_EINVAL,
               "the context's options changed since the saved forward");
-    PairGeom pg = c.pair_geom();
+    const PairGeom pg = c.pair_geom();    // padded rows (the contraction's operands)
+    const PairGeom pk = c.geom64(B);      // the K products' operands
+    double* const uk = c.ubuf64(B);
     const GemmDims& d = c.kd();
     const double lo = c.poly_lo, hi = c.poly_hi;
     const size_t vec = (size_t)B * nvc;
@@ -302,10 +304,10 @@ gwl_status vjp_run(gwl_ctx* ctx, VjpMode mode, const int* qp_states, int n_qp, i
       c.cast(B, Ti, GWL_FP64);
       for (int j = 0; j < g; ++j) {
         c.k_product(B, GWL_FP64, S, VTi + (size_t)j * fld);
-        combine<double, double>(pg, B, S, reinterpret_cast<const double*>(c.ypart.p),
+        combine<double, double>(pk, B, S, reinterpret_cast<const double*>(c.ypart.p),
                                 Ti + (size_t)j * vec, j > 0 ? Ti + (size_t)(j - 1) * vec : nullptr,
                                 Ti + (size_t)(j + 1) * vec, w, j == 0 ? 1 : 2, lo, hi,
-                                c.cheb[0], c.cheb[j + 1], j + 1 < g ? c.u64.p : nullptr, st,
+                                c.cheb[0], c.cheb[j + 1], j + 1 < g ? uk : nullptr, st,
                                 KTi + (size_t)j * vec);
       }
     };
@@ -415,11 +417,11 @@ gwl_status vjp_run(gwl_ctx* ctx, VjpMode mode, const int* qp_states, int n_qp, i
         c.cast(B, Sv.p + (size_t)g * vec, GWL_FP64);
         for (int j = g; j >= 1; --j) {
           c.k_product(B, GWL_FP64, S, VS.p + (size_t)(j - 1) * fld);
-          adj_combine(pg, B, S, reinterpret_cast<const double*>(c.ypart.p),
+          adj_combine(pk, B, S, reinterpret_cast<const double*>(c.ypart.p),
                       Sv.p + (size_t)j * vec, j < g ? Sv.p + (size_t)(j + 1) * vec : nullptr,
                       wbar.p, c.cheb[j - 1], j >= 2 ? 2.0 : 1.0, lo, hi,
                       Sv.p + (size_t)(j - 1) * vec, KS.p + (size_t)j * vec,
-                      j - 1 >= 1 ? c.u64.p : nullptr, st);
+                      j - 1 >= 1 ? uk : nullptr, st);
         }
         // C_bar = (2/(hi-lo)) [sum_{j>=2} 2 s_j t_{j-1}^T + s_1 t_0^T]: its Delta part
         // now, its coupling part as the pair-vector operands of the contraction
@@ -462,7 +464,7 @@ gwl_status vjp_run(gwl_ctx* ctx, VjpMode mode, const int* qp_states, int n_qp, i
       // orbital terms of the coupling integrals (nm|vc) = dV sum_r rho_vc V[phi_n phi_m]:
       // k_bar with V[phi_n phi_m] through the contraction, and the potential of
       // rho(k_bar) with phi_m (for phi_n) and phi_n (for phi_m)
-      c.cast(B, kbar.p, GWL_FP64, true);
+      cast_u<double>(c.pair_geom(true), B, kbar.p, nvc, c.u64.p, st);
       adj_zgemm(d, c.nv, ZSeg{Vnm, c.u64.p, nbk}, ZSeg{nullptr, nullptr, 0}, psi_c_rc,
                 psi_v_rv, c.dv, grad_c, gvpart.p, st);
       c.potential64(nbk, c.vpot64.p);
