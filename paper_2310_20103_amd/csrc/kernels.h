@@ -40,6 +40,14 @@ void poisson_launch(const PoissonGeom<T>& g, const T* rin, long ld_in, long part
                     hipStream_t st, unsigned* xmax = nullptr, int* vexp = nullptr,
                     int pexp = 0, f16_t* rout16 = nullptr);
 
+// The same on in-place plane passes (fft_plane.hip): true if the grid's edges
+// and planes are among those it covers, false with nothing done otherwise.
+template <typename T>
+bool poisson_planes(const PoissonGeom<T>& g, const T* rin, long ld_in, long part_stride,
+                    int nparts, T* rout, long ld_out, int nf, cplx<T>* scratch, hipStream_t st,
+                    unsigned* xmax, int* vexp, int pexp, f16_t* rout16);
+void plane_prepare_device();  // once per device, from poisson_prepare_device
+
 // ---------------------------------------------------------------- GEMMs
 // Padded operand layouts (NRp, NVp, NCp multiples of the tile sizes):
 //   psi_c_rc [NRp][NCp]  (GEMM1 B operand, c contiguous)
