@@ -216,6 +216,8 @@ struct gwl_ctx {
   DevBuf<double> hbuf;         // [cap][cap_L + 1]
   DevBuf<double> rw_n0, rw_part;  // reorthogonalisation scratch [cap], [cap][part_len]
   DevBuf<int> rw_skip;            // [cap]
+  DevBuf<double> xe_part, xe_out;  // exchange: energy shares, energy per state
+  DevBuf<int> xe_rows;             // and the orbital rows of its products
   DevBuf<int> s_pair, s_k, s_len, s_dead, s_slots, s_m, s_n, s_act;
   // while set, GEMM operand rows map to these slots (see PairGeom::rows)
   const int* cur_rows = nullptr;
@@ -625,9 +627,11 @@ struct gwl_ctx {
     double* rp = reinterpret_cast<double*>(rho.p);
     double* vp = vpot64.p;
     double* yp = reinterpret_cast<double*>(ypart.p);
-    pair_product(psi_t.p, gd.nrp, (int)nr, mrow, nrow, cnt, rp, stream);
-    poisson_launch<double>(pg64, rp, gd.nrp, 0, 1, vp, gd.nrp, cnt,
-                           reinterpret_cast<cplx<double>*>(fftx.p), stream);
+    cplx<double>* fx = reinterpret_cast<cplx<double>*>(fftx.p);
+    if (!poisson_products(pg64, psi_t.p, gd.nrp, mrow, nrow, vp, gd.nrp, cnt, fx, stream)) {
+      pair_product(psi_t.p, gd.nrp, (int)nr, mrow, nrow, cnt, rp, stream);
+      poisson_launch<double>(pg64, rp, gd.nrp, 0, 1, vp, gd.nrp, cnt, fx, stream);
+    }
     // (the coupling integrals stay on the grid when the K product is on the points)
     const int S = isdf_on && !splitk && pd(cnt) ? gemm2_pd_split(gd, cnt)
                                                 : auto_splitk(cnt, GWL_FP64);

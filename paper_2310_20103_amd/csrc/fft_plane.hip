@@ -272,13 +272,52 @@ __device__ inline void stage_tables(cplx<T>* tw, const PlaneGeom<T>& g) {
 // for long lines in FP64
 constexpr int max_threads(bool is_long, size_t real) { return is_long && real == 8 ? 512 : 1024; }
 
-// Forward plane pass: fields 2p and 2p + 1 (each the sum of nparts GEMM
-// partial densities) packed, z lines then y lines of the plane at x.
-template <typename T, bool LONG>
+// Fields in, for the forward plane pass: sums of nparts GEMM partial densities,
+template <typename T>
+struct FieldSums {
+  const T* in;
+  long ld, part_stride;
+  int nparts, nf;
+  __device__ bool has(int f) const { return f < nf; }
+  // v[i] = value e0 + step i of field f
+  template <int R, typename V>
+  __device__ void load(int f, long e0, int step, V set) const {
+    const T* p = in + f * ld + e0;
+    T v[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) v[i] = p[step * i];
+    for (int q = 1; q < nparts; ++q)
+#pragma unroll
+      for (int i = 0; i < R; ++i) v[i] += p[q * part_stride + step * i];
+#pragma unroll
+    for (int i = 0; i < R; ++i) set(i, v[i]);
+  }
+};
+// or products of two orbital rows (n[f] < 0: no field).
+struct RowProducts {
+  const double* psi;
+  long ld;
+  const int *m, *n;
+  int nf;
+  __device__ bool has(int f) const { return f < nf && n[f] >= 0; }
+  template <int R, typename V>
+  __device__ void load(int f, long e0, int step, V set) const {
+    const double* a = psi + m[f] * ld + e0;
+    const double* b = psi + n[f] * ld + e0;
+    double v[R], w[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) v[i] = a[step * i], w[i] = b[step * i];
+#pragma unroll
+    for (int i = 0; i < R; ++i) set(i, v[i] * w[i]);
+  }
+};
+
+// Forward plane pass: fields 2p and 2p + 1 packed, z lines then y lines of the
+// plane at x.
+template <typename T, bool LONG, typename In>
 __global__ void __launch_bounds__(max_threads(LONG, sizeof(T)))
 __attribute__((amdgpu_waves_per_eu(min_waves(LONG, sizeof(T)))))
-plane_forward(PlaneGeom<T> g, const T* __restrict__ rin, long ld, long part_stride, int nparts,
-              int nf, cplx<T>* __restrict__ X, unsigned* __restrict__ xmax) {
+plane_forward(PlaneGeom<T> g, In in, cplx<T>* __restrict__ X, unsigned* __restrict__ xmax) {
   extern __shared__ unsigned char smem_raw[];
   const int P = g.nz | 1;  // LDS row: odd, for the steps with consecutive threads on consecutive rows
   cplx<T>* buf = reinterpret_cast<cplx<T>*>(smem_raw);
@@ -286,9 +325,8 @@ plane_forward(PlaneGeom<T> g, const T* __restrict__ rin, long ld, long part_stri
   cplx<T>* twz = twy + g.ny;
   stage_tables(twy, g);
   const int x = blockIdx.x, pair = blockIdx.y, t = threadIdx.x, nt = blockDim.x;
-  const bool two = 2 * pair + 1 < nf;
-  const T* f0 = rin + (long)(2 * pair) * ld + (long)x * g.ny * g.nz;
-  const T* f1 = f0 + (two ? ld : 0);
+  const bool two = in.has(2 * pair + 1);
+  const long plane = (long)x * g.ny * g.nz;
   if (xmax && x == 0 && t == 0) xmax[pair] = 0u;
   __syncthreads();
   with_length<LONG>(g.nz, [&](auto R_) {
@@ -296,19 +334,14 @@ plane_forward(PlaneGeom<T> g, const T* __restrict__ rin, long ld, long part_stri
     constexpr int R1 = R::R1, R2 = R::R2;
     for (int b = t; b < g.ny * R2; b += nt) {
       const int y = b / R2, j = b - y * R2;
-      const int e0 = y * g.nz + j;
+      const long e0 = plane + y * g.nz + j;
       cplx<T> v[R1];
+      in.template load<R1>(2 * pair, e0, R2, [&](int i, T a) { v[i].x = a; });
+      if (two)
+        in.template load<R1>(2 * pair + 1, e0, R2, [&](int i, T a) { v[i].y = a; });
+      else
 #pragma unroll
-      for (int a = 0; a < R1; ++a) v[a] = {f0[e0 + R2 * a], f1[e0 + R2 * a]};
-      for (int q = 1; q < nparts; ++q)
-#pragma unroll
-        for (int a = 0; a < R1; ++a) {
-          v[a].x += f0[q * part_stride + e0 + R2 * a];
-          v[a].y += f1[q * part_stride + e0 + R2 * a];
-        }
-      if (!two)
-#pragma unroll
-        for (int a = 0; a < R1; ++a) v[a].y = 0;
+        for (int i = 0; i < R1; ++i) v[i].y = 0;
       step1<R>(v, twz);
       cplx<T>* row = buf + y * P + j;
 #pragma unroll
@@ -531,6 +564,77 @@ x_pass(cplx<T>* __restrict__ X, int nx, int nz, int lx, int nzb, long nr, FastDi
   if (xmax) block_max(mx, &xmax[pair]);
 }
 
+// The forward half of the x pass for the energies dV sum_r rho V = dV sum_k
+// (v(G)/N) |rho_k|^2: part[pair][block] = this block's share of the sum of both
+// fields' energies (the cross terms of the packed spectrum cancel between k
+// and -k), nothing is written back.  HBM-bound: with the products formed in the
+// forward pass, 1,024 products of 64^3 cross memory as orbital rows in, spectrum
+// out and in (8.6 GB): 1.48 ms, against 12.3 ms for product, whole solve and a
+// grid sum with one block per field.
+template <bool LONG>
+__global__ void __launch_bounds__(max_threads(LONG, 8))
+x_energy(const cplx<double>* __restrict__ X, int nx, int nz, int lx, int nzb, long nr, FastDiv dlx,
+         const cplx<double>* __restrict__ twx, const double* __restrict__ g2x,
+         const double* __restrict__ g2y, const double* __restrict__ g2z, double vscale,
+         double* __restrict__ part) {
+  extern __shared__ unsigned char smem_raw[];
+  cplx<double>* buf = reinterpret_cast<cplx<double>*>(smem_raw);
+  cplx<double>* tw = buf + nx * lx;
+  double* g2s = reinterpret_cast<double*>(tw + nx);
+  const int t = threadIdx.x, nt = blockDim.x, pair = blockIdx.y;
+  for (int i = t; i < nx; i += nt) {
+    tw[i] = twx[i];
+    g2s[i] = g2x[i];
+  }
+  const int ky = blockIdx.x / nzb, z0 = (blockIdx.x - ky * nzb) * lx;
+  const int nl = min(lx, nz - z0);
+  const cplx<double>* Xp = X + (long)pair * nr + (long)ky * nx * nz + z0;
+  const double gy = g2y[ky];
+  double sum = 0.0;
+  __syncthreads();
+  with_length<LONG>(nx, [&](auto R_) {
+    typedef decltype(R_) R;
+    constexpr int R1 = R::R1, R2 = R::R2;
+    for (int b = t; b < lx * R2; b += nt) {
+      const int j = dlx.div(b), c = b - j * lx;
+      const cplx<double>* i = Xp + (c < nl ? c : 0);
+      cplx<double> v[R1];
+#pragma unroll
+      for (int a = 0; a < R1; ++a) v[a] = i[(j + R2 * a) * nz];
+      step1<R>(v, tw);
+#pragma unroll
+      for (int r = 0; r < R1; ++r) buf[(j + R2 * r) * lx + c] = v[r];
+    }
+    __syncthreads();
+    for (int b = t; b < lx * R1; b += nt) {
+      const int r = dlx.div(b), c = b - r * lx;
+      if (c >= nl) continue;
+      const double gz = g2z[z0 + c];
+      cplx<double> v[R2];
+#pragma unroll
+      for (int j = 0; j < R2; ++j) v[j] = buf[(j + R2 * r) * lx + c];
+      step2<R>(v, tw, r);
+#pragma unroll
+      for (int k = 0; k < R2; ++k) {
+        const double g2 = g2s[r + R1 * k] + gy + gz;
+        const double f = g2 > 0.0 ? vscale / g2 : 0.0;
+        sum += f * (v[k].x * v[k].x + v[k].y * v[k].y);
+      }
+    }
+  });
+  // fixed order: lanes of a wave, then the waves
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+  __shared__ double ws[16];
+  if ((t & 63) == 0) ws[t >> 6] = sum;
+  __syncthreads();
+  if (t == 0) {
+    double a = 0.0;
+    for (int i = 0; i < nt >> 6; ++i) a += ws[i];
+    part[(long)pair * gridDim.x + blockIdx.x] = a;
+  }
+}
+
 constexpr size_t kLdsMax = 160 * 1024;  // one CU's LDS
 // LDS of an x-pass block at most: two blocks share a CU
 constexpr size_t kXLds = 72 * 1024;
@@ -548,8 +652,14 @@ size_t x_lds(int nx, int lx) { return ((size_t)nx * lx + nx) * sizeof(cplx<T>) +
 template <typename T, bool LONG>
 void allow_lds() {
   const int lim = (int)kLdsMax;
-  GWL_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&plane_forward<T, LONG>),
+  GWL_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&plane_forward<T, LONG, FieldSums<T>>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, lim));
+  if constexpr (sizeof(T) == 8) {
+    GWL_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&plane_forward<T, LONG, RowProducts>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, lim));
+    GWL_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&x_energy<LONG>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kXLds));
+  }
   GWL_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&plane_inverse<T, LONG>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, lim));
   GWL_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&x_pass<T, LONG>),
@@ -565,17 +675,28 @@ void plane_prepare_device() {
   allow_lds<double, true>();
 }
 
+namespace {
+
+// Launch shapes of a grid's passes.
 template <typename T>
-bool poisson_planes(const PoissonGeom<T>& g, const T* rin, long ld_in, long part_stride, int nparts,
-                    T* rout, long ld_out, int nf, cplx<T>* scratch, hipStream_t st, unsigned* xmax,
-                    int* vexp, int pexp, f16_t* rout16) {
-  int r1x, r2x, r1y, r2y, r1z, r2z;
-  bool lgx, lgy, lgz;
-  if (!fft_split(g.nx, r1x, r2x, lgx) || !fft_split(g.ny, r1y, r2y, lgy) ||
-      !fft_split(g.nz, r1z, r2z, lgz) || plane_lds<T>(g.ny, g.nz) > kLdsMax)
-    return false;
-  const bool lg = lgy || lgz;
+struct Plan {
   PlaneGeom<T> p;
+  bool ok, lg, lgx;      // covered; long y or z lines; long x lines
+  int nt, ntx, lx, nzb;  // threads, kz columns per x block and blocks per slab
+  size_t sm, smx;
+};
+
+template <typename T>
+Plan<T> plan_for(const PoissonGeom<T>& g) {
+  Plan<T> q{};
+  int r1x, r2x, r1y, r2y, r1z, r2z;
+  bool lgy, lgz;
+  if (!fft_split(g.nx, r1x, r2x, q.lgx) || !fft_split(g.ny, r1y, r2y, lgy) ||
+      !fft_split(g.nz, r1z, r2z, lgz) || plane_lds<T>(g.ny, g.nz) > kLdsMax)
+    return q;
+  q.ok = true;
+  q.lg = lgy || lgz;
+  PlaneGeom<T>& p = q.p;
   p.nx = g.nx;
   p.ny = g.ny;
   p.nz = g.nz;
@@ -590,33 +711,91 @@ bool poisson_planes(const PoissonGeom<T>& g, const T* rin, long ld_in, long part
   p.d1z = fast_div(r1z);
   p.twy = g.twy;
   p.twz = g.twz;
+  q.nt = threads_for<T>(std::max(g.nz * std::max(r1y, r2y), g.ny * std::max(r1z, r2z)), q.lg);
+  q.sm = plane_lds<T>(g.ny, g.nz);
+  q.lx = g.nz;
+  while (q.lx > 8 && x_lds<T>(g.nx, q.lx) > kXLds) q.lx = (q.lx + 1) / 2;
+  q.nzb = ceil_div(g.nz, q.lx);
+  q.ntx = threads_for<T>(q.lx * std::max(r1x, r2x), q.lgx);
+  q.smx = x_lds<T>(g.nx, q.lx);
+  return q;
+}
+
+template <typename T, typename In>
+void forward(const Plan<T>& q, const In& in, int npairs, cplx<T>* X, unsigned* xmax,
+             hipStream_t st) {
+  const dim3 grid(q.p.nx, npairs);
+  if (q.lg)
+    plane_forward<T, true, In><<<grid, q.nt, q.sm, st>>>(q.p, in, X, xmax);
+  else
+    plane_forward<T, false, In><<<grid, q.nt, q.sm, st>>>(q.p, in, X, xmax);
+}
+
+template <typename T>
+void rest(const PoissonGeom<T>& g, const Plan<T>& q, int nf, cplx<T>* X, const PlaneOut<T>& out,
+          unsigned* xmax, hipStream_t st) {
   const int npairs = (nf + 1) / 2;
-  const int nt = threads_for<T>(std::max(g.nz * std::max(r1y, r2y), g.ny * std::max(r1z, r2z)), lg);
-  const size_t sm = plane_lds<T>(g.ny, g.nz);
-  int lx = g.nz;
-  while (lx > 8 && x_lds<T>(g.nx, lx) > kXLds) lx = (lx + 1) / 2;
-  const int nzb = ceil_div(g.nz, lx);
-  const int ntx = threads_for<T>(lx * std::max(r1x, r2x), lgx);
-  const size_t smx = x_lds<T>(g.nx, lx);
-  const dim3 gp(g.nx, npairs), gx(g.ny * nzb, npairs);
-  const PlaneOut<T> out{rout, vexp ? rout16 : nullptr, ld_out, xmax, vexp, pexp};
-  unsigned* xm = vexp ? xmax : nullptr;
-  if (lg)
-    plane_forward<T, true><<<gp, nt, sm, st>>>(p, rin, ld_in, part_stride, nparts, nf, scratch, xm);
+  const dim3 gx(g.ny * q.nzb, npairs), gp(g.nx, npairs);
+  if (q.lgx)
+    x_pass<T, true><<<gx, q.ntx, q.smx, st>>>(X, g.nx, g.nz, q.lx, q.nzb, q.p.nr, fast_div(q.lx),
+                                              g.twx, g.g2x, g.g2y, g.g2z, g.vscale, xmax);
   else
-    plane_forward<T, false><<<gp, nt, sm, st>>>(p, rin, ld_in, part_stride, nparts, nf, scratch, xm);
-  if (lgx)
-    x_pass<T, true><<<gx, ntx, smx, st>>>(scratch, g.nx, g.nz, lx, nzb, p.nr, fast_div(lx), g.twx,
-                                          g.g2x, g.g2y, g.g2z, g.vscale, xm);
+    x_pass<T, false><<<gx, q.ntx, q.smx, st>>>(X, g.nx, g.nz, q.lx, q.nzb, q.p.nr, fast_div(q.lx),
+                                               g.twx, g.g2x, g.g2y, g.g2z, g.vscale, xmax);
+  if (q.lg)
+    plane_inverse<T, true><<<gp, q.nt, q.sm, st>>>(q.p, X, nf, out);
   else
-    x_pass<T, false><<<gx, ntx, smx, st>>>(scratch, g.nx, g.nz, lx, nzb, p.nr, fast_div(lx), g.twx,
-                                           g.g2x, g.g2y, g.g2z, g.vscale, xm);
-  if (lg)
-    plane_inverse<T, true><<<gp, nt, sm, st>>>(p, scratch, nf, out);
-  else
-    plane_inverse<T, false><<<gp, nt, sm, st>>>(p, scratch, nf, out);
+    plane_inverse<T, false><<<gp, q.nt, q.sm, st>>>(q.p, X, nf, out);
   GWL_HIP(hipGetLastError());
+}
+
+}  // namespace
+
+template <typename T>
+bool poisson_planes(const PoissonGeom<T>& g, const T* rin, long ld_in, long part_stride, int nparts,
+                    T* rout, long ld_out, int nf, cplx<T>* scratch, hipStream_t st, unsigned* xmax,
+                    int* vexp, int pexp, f16_t* rout16) {
+  const Plan<T> q = plan_for<T>(g);
+  if (!q.ok) return false;
+  unsigned* xm = vexp ? xmax : nullptr;
+  forward(q, FieldSums<T>{rin, ld_in, part_stride, nparts, nf}, (nf + 1) / 2, scratch, xm, st);
+  rest(g, q, nf, scratch, PlaneOut<T>{rout, vexp ? rout16 : nullptr, ld_out, xmax, vexp, pexp}, xm,
+       st);
   return true;
+}
+
+bool poisson_products(const PoissonGeom<double>& g, const double* psi, long ld, const int* m,
+                      const int* n, double* rout, long ld_out, int nf, cplx<double>* scratch,
+                      hipStream_t st) {
+  const Plan<double> q = plan_for<double>(g);
+  if (!q.ok) return false;
+  forward(q, RowProducts{psi, ld, m, n, nf}, (nf + 1) / 2, scratch, (unsigned*)nullptr, st);
+  rest(g, q, nf, scratch, PlaneOut<double>{rout, nullptr, ld_out, nullptr, nullptr, 0},
+       (unsigned*)nullptr, st);
+  return true;
+}
+
+int product_energy_blocks(const PoissonGeom<double>& g) {
+  const Plan<double> q = plan_for<double>(g);
+  return q.ok ? g.ny * q.nzb : 0;
+}
+
+void product_energies(const PoissonGeom<double>& g, const double* psi, long ld, const int* m,
+                      const int* n, int npairs, double* part, cplx<double>* scratch,
+                      hipStream_t st) {
+  if (npairs <= 0) return;
+  const Plan<double> q = plan_for<double>(g);
+  forward(q, RowProducts{psi, ld, m, n, 2 * npairs}, npairs, scratch, (unsigned*)nullptr, st);
+  const dim3 gx(g.ny * q.nzb, npairs);
+  if (q.lgx)
+    x_energy<true><<<gx, q.ntx, q.smx, st>>>(scratch, g.nx, g.nz, q.lx, q.nzb, q.p.nr,
+                                             fast_div(q.lx), g.twx, g.g2x, g.g2y, g.g2z, g.vscale,
+                                             part);
+  else
+    x_energy<false><<<gx, q.ntx, q.smx, st>>>(scratch, g.nx, g.nz, q.lx, q.nzb, q.p.nr,
+                                              fast_div(q.lx), g.twx, g.g2x, g.g2y, g.g2z, g.vscale,
+                                              part);
+  GWL_HIP(hipGetLastError());
 }
 
 template bool poisson_planes<float>(const PoissonGeom<float>&, const float*, long, long, int, float*,

@@ -679,36 +679,57 @@ gwl_status gwl_sigma_x(gwl_ctx* ctx, const int* qp_states, int n_qp, double* sig
       GWL_CHECK(qp_states[i] >= 0 && qp_states[i] < ctx->n_orb, GWL_EINVAL,
                 "qp state out of range");
     gwl_ctx& c = *ctx;
-    const int nv = c.nv;
-    const int chunk = std::min(nv, 64);
+    // The products phi_v phi_m of up to 65,536 fields' worth of states in one
+    // list, an even number per state (a packed transform holds two products of
+    // one state; the list of an odd N_v ends in a zero field), in chunks of the
+    // work buffers' size.
+    const int nv = c.nv, per = nv + (nv & 1);
+    const int group = std::min(n_qp, std::max(1, 65536 / per));
+    const int chunk = (int)std::min<long>((long)group * per, 64);
     c.ensure_work(chunk, 1, false);
-    DevBuf<double> e;
-    e.ensure((size_t)nv);
-    std::vector<int> mr(chunk), vr(chunk);
-    std::vector<double> he(nv);
-    double* rp = reinterpret_cast<double*>(c.rho.p);
-    for (int q = 0; q < n_qp; ++q) {
-      for (int v0 = 0; v0 < nv; v0 += chunk) {
-        const int cnt = std::min(chunk, nv - v0);
-        for (int i = 0; i < cnt; ++i) {
-          mr[i] = c.orb_row(qp_states[q]);
-          vr[i] = c.orb_row(v0 + i);
+    c.xe_rows.ensure(2 * (size_t)group * per);
+    c.xe_out.ensure(group);
+    cplx<double>* fx = reinterpret_cast<cplx<double>*>(c.fftx.p);
+    const int nblk = product_energy_blocks(c.pg64);
+    c.xe_part.ensure(nblk > 0 ? (size_t)group * per / 2 * nblk : (size_t)group * nv * kEnergyParts);
+    for (int q0 = 0; q0 < n_qp; q0 += group) {
+      const int nq = std::min(group, n_qp - q0), total = nq * per;
+      std::vector<int> rows(2 * (size_t)total);
+      for (int q = 0; q < nq; ++q)
+        for (int v = 0; v < per; ++v) {
+          rows[(size_t)q * per + v] = c.orb_row(qp_states[q0 + q]);
+          rows[(size_t)total + (size_t)q * per + v] = v < nv ? c.orb_row(v) : -1;
         }
-        GWL_HIP(hipStreamSynchronize(c.stream));
-        GWL_HIP(hipMemcpy(c.s_m.p, mr.data(), cnt * sizeof(int), hipMemcpyHostToDevice));
-        GWL_HIP(hipMemcpy(c.s_n.p, vr.data(), cnt * sizeof(int), hipMemcpyHostToDevice));
-        pair_product(c.psi_t.p, c.gd.nrp, (int)c.nr, c.s_m.p, c.s_n.p, cnt, rp, c.stream);
-        poisson_launch<double>(c.pg64, rp, c.gd.nrp, 0, 1, c.vpot64.p, c.gd.nrp, cnt,
-                               reinterpret_cast<cplx<double>*>(c.fftx.p), c.stream);
-        pair_energy(rp, c.vpot64.p, c.gd.nrp, (int)c.nr, c.dv, cnt, e.p + v0, c.stream);
+      GWL_HIP(hipMemcpyAsync(c.xe_rows.p, rows.data(), rows.size() * sizeof(int),
+                             hipMemcpyHostToDevice, c.stream));
+      const int *mr = c.xe_rows.p, *vr = mr + total;
+      if (nblk > 0) {
+        // the energies in frequency space: a forward transform, nothing back
+        for (int f0 = 0; f0 < total; f0 += chunk)
+          product_energies(c.pg64, c.psi_t.p, c.gd.nrp, mr + f0, vr + f0,
+                           std::min(chunk, total - f0) / 2, c.xe_part.p + (size_t)(f0 / 2) * nblk,
+                           fx, c.stream);
+        sum_rows(c.xe_part.p, (long)(per / 2) * nblk, nq, c.dv, c.xe_out.p, c.stream);
+      } else {
+        // sum_r rho V on the grid, state by state
+        double* rp = reinterpret_cast<double*>(c.rho.p);
+        for (int q = 0; q < nq; ++q)
+          for (int v0 = 0; v0 < nv; v0 += chunk) {
+            const int cnt = std::min(chunk, nv - v0);
+            const size_t f0 = (size_t)q * per + v0;
+            pair_product(c.psi_t.p, c.gd.nrp, (int)c.nr, mr + f0, vr + f0, cnt, rp, c.stream);
+            poisson_launch<double>(c.pg64, rp, c.gd.nrp, 0, 1, c.vpot64.p, c.gd.nrp, cnt, fx,
+                                   c.stream);
+            pair_energy(rp, c.vpot64.p, c.gd.nrp, (int)c.nr, cnt,
+                        c.xe_part.p + ((size_t)q * nv + v0) * kEnergyParts, c.stream);
+          }
+        sum_rows(c.xe_part.p, (long)nv * kEnergyParts, nq, c.dv, c.xe_out.p, c.stream);
       }
-      GWL_HIP(hipMemcpyAsync(he.data(), e.p, nv * sizeof(double), hipMemcpyDeviceToHost,
-                             c.stream));
+      GWL_HIP(hipMemcpyAsync(sigma_x_out + q0, c.xe_out.p, nq * sizeof(double),
+                             hipMemcpyDeviceToHost, c.stream));
       GWL_HIP(hipStreamSynchronize(c.stream));
-      double sx = 0.0;
-      for (int v = 0; v < nv; ++v) sx -= he[v];
-      sigma_x_out[q] = sx * kHartreeEv;
     }
+    for (int q = 0; q < n_qp; ++q) sigma_x_out[q] *= -kHartreeEv;
     GWL_CHECK(finite_all(sigma_x_out, n_qp), GWL_ENUMERIC, "non-finite exchange self-energy");
   });
 }

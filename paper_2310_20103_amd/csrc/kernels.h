@@ -46,6 +46,18 @@ template <typename T>
 bool poisson_planes(const PoissonGeom<T>& g, const T* rin, long ld_in, long part_stride,
                     int nparts, T* rout, long ld_out, int nf, cplx<T>* scratch, hipStream_t st,
                     unsigned* xmax, int* vexp, int pexp, f16_t* rout16);
+// The solve for nf products of orbital rows psi[m[f]] psi[n[f]] (device row
+// lists), formed as they are read (n[f] < 0: a zero field).
+bool poisson_products(const PoissonGeom<double>& g, const double* psi, long ld, const int* m,
+                      const int* n, double* rout, long ld_out, int nf, cplx<double>* scratch,
+                      hipStream_t st);
+// Energies sum_r rho V of such products, two rows of the lists per pair: part
+// [npairs][product_energy_blocks] holds shares of both products' sum.  0
+// blocks: the grid is not covered.
+int product_energy_blocks(const PoissonGeom<double>& g);
+void product_energies(const PoissonGeom<double>& g, const double* psi, long ld, const int* m,
+                      const int* n, int npairs, double* part, cplx<double>* scratch,
+                      hipStream_t st);
 void plane_prepare_device();  // once per device, from poisson_prepare_device
 
 // ---------------------------------------------------------------- GEMMs
@@ -176,9 +188,13 @@ struct PairGeom {
 void pair_product(const double* psi_t, long ld, int nr, const int* m_idx, const int* n_idx,
                   int cnt, double* rho, hipStream_t st);
 
-// out[i] = dv sum_{r < nr} rho_i(r) V_i(r) for cnt fields (row stride ld).
-void pair_energy(const double* rho, const double* vpot, long ld, int nr, double dv, int cnt,
-                 double* out, hipStream_t st);
+// part[i][kEnergyParts] = shares of sum_{r < nr} rho_i(r) V_i(r) for cnt fields
+// (row stride ld).
+constexpr int kEnergyParts = 64;
+void pair_energy(const double* rho, const double* vpot, long ld, int nr, int cnt, double* part,
+                 hipStream_t st);
+// out[i] = scale sum of row i of part [rows][n], fixed order.
+void sum_rows(const double* part, long n, int rows, double scale, double* out, hipStream_t st);
 
 // out[i] = ||x_i||_2 for nrows rows of length n (FP64, fixed reduction order).
 void row_norm2(const double* x, long n, int nrows, double* out, hipStream_t st);

@@ -538,27 +538,39 @@ void pair_product(const double* psi_t, long ld, int nr, const int* m_idx, const 
   GWL_HIP(hipGetLastError());
 }
 
-// out[i] = dv sum_{r < nr} rho_i(r) V_i(r), fixed reduction order.
-__global__ void pair_energy_kernel(const double* __restrict__ rho, const double* __restrict__ vpot,
-                                   long ld, int nr, double dv, double* __restrict__ out) {
-  __shared__ double red[NT];
-  const double* a = rho + (long)blockIdx.x * ld;
-  const double* b = vpot + (long)blockIdx.x * ld;
+// Sums in a fixed order: threads, lanes, waves (block of NT).
+__global__ void __launch_bounds__(NT)
+pair_energy_kernel(const double* __restrict__ rho, const double* __restrict__ vpot, long ld, int nr,
+                   double* __restrict__ part) {
+  __shared__ double sh[NT / 64];
+  const double* a = rho + (long)blockIdx.y * ld;
+  const double* b = vpot + (long)blockIdx.y * ld;
   double acc = 0.0;
-  for (long i = threadIdx.x; i < nr; i += blockDim.x) acc += a[i] * b[i];
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int w = NT / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[blockIdx.x] = dv * red[0];
+  for (long i = blockIdx.x * NT + threadIdx.x; i < nr; i += (long)gridDim.x * NT) acc += a[i] * b[i];
+  acc = block_sum(acc, sh);
+  if (threadIdx.x == 0) part[(long)blockIdx.y * gridDim.x + blockIdx.x] = acc;
 }
 
-void pair_energy(const double* rho, const double* vpot, long ld, int nr, double dv, int cnt,
-                 double* out, hipStream_t st) {
+__global__ void __launch_bounds__(NTS)
+sum_rows_kernel(const double* __restrict__ part, long n, double scale, double* __restrict__ out) {
+  __shared__ double sh[NTS / 64];
+  const double* p = part + (long)blockIdx.x * n;
+  double acc = 0.0;
+  for (long i = threadIdx.x; i < n; i += NTS) acc += p[i];
+  acc = block_sum(acc, sh);
+  if (threadIdx.x == 0) out[blockIdx.x] = scale * acc;
+}
+
+void pair_energy(const double* rho, const double* vpot, long ld, int nr, int cnt, double* part,
+                 hipStream_t st) {
   if (cnt <= 0) return;
-  pair_energy_kernel<<<cnt, NT, 0, st>>>(rho, vpot, ld, nr, dv, out);
+  pair_energy_kernel<<<dim3(kEnergyParts, cnt), NT, 0, st>>>(rho, vpot, ld, nr, part);
+  GWL_HIP(hipGetLastError());
+}
+
+void sum_rows(const double* part, long n, int rows, double scale, double* out, hipStream_t st) {
+  if (rows <= 0) return;
+  sum_rows_kernel<<<rows, NTS, 0, st>>>(part, n, scale, out);
   GWL_HIP(hipGetLastError());
 }
 
