@@ -341,23 +341,41 @@ struct gwl_ctx {
                     std::max(gemm1_f64m_vtiles(gd), gemm1_f16_vtiles(gd)));
   }
 
-  // Split of the grid sum in the second GEMM: enough blocks to give every
-  // CU several (the kernels run one wave per SIMD), each block keeping a
-  // K range of at least 2048 grid points.
+  // Split of the grid sum in the second GEMM.
   int auto_splitk(int nb, int prec) const {
     if (splitk > 0) return splitk;
-    if (prec == GWL_FP64 && pd(nb)) return gemm2_pd_split(kd(), nb);  // (not tuned)
-    if (tuned[prec].B == nb && tuned[prec].S > 0) return tuned[prec].S;
-    return heuristic_splitk(nb, prec);
+    const bool model = prec == GWL_FP64 && fp64_kernel;  // (these kernels' rules need no tuning)
+    if (!model && tuned[prec].B == nb && tuned[prec].S > 0) return tuned[prec].S;
+    return heuristic_splitk(nb, prec, kd());
   }
-  int heuristic_splitk(int nb, int prec) const {
-    const GemmDims& d = kd();
+  int heuristic_splitk(int nb, int prec, const GemmDims& d) const {
     if (prec == GWL_FP64 && pd(nb)) return gemm2_pd_split(d, nb);
+    if (fp64_kernel && prec == GWL_FP64) {
+      // The split that a model of the FP64 kernel's time prefers: a CU works
+      // through its blocks at 1.9 us per K step of 16 (64 matrix instructions
+      // per SIMD; 8 % more when one block has the CU to itself), each block
+      // costs about five more steps, and every partial tile is written and
+      // read once.  It picks the best measured split where tried: 12 vectors of
+      // 64 + 256 orbitals at 48^3 42 of {16, 21, 32, 42}, 64 vectors 8 of {4, 8,
+      // 16, 24}, on 1,280 ISDF points 4 of {1..6, 8}.
+      const long tiles = gemm2_f64m_blocks(d, nb);
+      const int smax = (int)std::max<long>(1, std::min<long>(max_splitk(nb), d.nrp / 128));
+      int best = 1;
+      double least = 1e300;
+      for (int s = 1; s <= smax; ++s) {
+        const long per_cu = ceil_div(tiles * s, 256);
+        const double us = per_cu * (ceil_div(d.nrp, 16L * s) + 5) * 1.9 * (per_cu == 1 ? 1.08 : 1.0) +
+                          s * tiles * (2.0 * 128 * 128 * 8 / 4.8e6);
+        if (us < least) {
+          least = us;
+          best = s;
+        }
+      }
+      return best;
+    }
     long blocks;
     if (!fp64_kernel)
       blocks = (long)nb * (d.nvp / 64) * ceil_div(d.ncp, 64);
-    else if (prec == GWL_FP64)
-      blocks = gemm2_f64m_blocks(d, nb);
     else
       blocks = gemm2_f16_blocks(d, nb, bf16_tile);
     int s = 1;
@@ -365,6 +383,10 @@ struct gwl_ctx {
     while (blocks * s < 1024 && s < 32 && (long)d.nrp / (s * 2) >= 512) s *= 2;
     return s;
   }
+  // Splits the partial sums' buffer has room for, whatever the batch it was
+  // sized for: small batches may take more (they have few tiles).
+  static int max_splitk(int nb) { return nb < 32 ? 64 : 32; }
+  static size_t split_rows(int cap) { return std::max((size_t)32 * cap, (size_t)64 * std::min(cap, 31)); }
 
   void ensure_work(int nb, int Lrows, bool need_basis) {
     const long nvpc = (long)gd.nvp * gd.ncp;
@@ -385,7 +407,7 @@ struct gwl_ctx {
       xmax32.ensure((size_t)alloc_rows_v(nb, gd.nvp));
       vexp32.ensure((size_t)alloc_rows_v(nb, gd.nvp));
       fftx.ensure((size_t)((nb + 1) / 2) * nr * 16);
-      ypart.ensure((size_t)32 * nb * nvpc * 8);
+      ypart.ensure(split_rows(nb) * nvpc * 8);
       s_pair.ensure(nb);
       s_k.ensure(nb);
       s_len.ensure(nb);
@@ -633,8 +655,8 @@ struct gwl_ctx {
       poisson_launch<double>(pg64, rp, gd.nrp, 0, 1, vp, gd.nrp, cnt, fx, stream);
     }
     // (the coupling integrals stay on the grid when the K product is on the points)
-    const int S = isdf_on && !splitk && pd(cnt) ? gemm2_pd_split(gd, cnt)
-                                                : auto_splitk(cnt, GWL_FP64);
+    const int S = isdf_on && !splitk ? heuristic_splitk(cnt, GWL_FP64, gd)
+                                     : auto_splitk(cnt, GWL_FP64);
     const double* pv = psi_t.p;
     const double* pc = psi_t.p + (size_t)gd.nvp * gd.nrp;
     second_gemm64(gd, cnt, S, pv, pc, vp, yp);
@@ -765,11 +787,11 @@ struct gwl_ctx {
         for (int B : cands) {
           if (B > bmax && B != cands[0]) break;
           ensure_work(B, 1, false);
-          const int s0 = heuristic_splitk(B, prec);
-          const bool flat = prec == GWL_FP64 && pd(B);  // (has its own split rule)
+          const int s0 = heuristic_splitk(B, prec, kd());
+          const bool model = prec == GWL_FP64 && fp64_kernel;
           for (int S : {s0 / 2, s0, s0 * 2}) {
-            if (flat && S != s0) continue;
-            if (!flat && (S < 1 || S > 32 || (S > 1 && (long)kd().nrp / S < 1024))) continue;
+            if (model && S != s0) continue;
+            if (!model && (S < 1 || S > 32 || (S > 1 && (long)kd().nrp / S < 1024))) continue;
             cast(B, q.p, prec);
             k_product(B, prec, S);  // warm
             GWL_HIP(hipEventRecord(e0, stream));
@@ -799,7 +821,7 @@ struct gwl_ctx {
       best.tile = tiles[0];
       bf16_tile = best.tile;
       best.B = std::max(1, std::min(bmax, 128));
-      best.S = heuristic_splitk(best.B, prec);
+      best.S = heuristic_splitk(best.B, prec, kd());
       best.us_per_vec = 0;
     }
     set_tile(best.tile);

@@ -74,81 +74,126 @@ __device__ inline bool gemm1_tile(int bid, int mt, int nt, long tile_bytes, int&
 }
 
 // ---------------------------------------------------------------- FP64
-constexpr int DM = 128, DN = 128, DK = 16, DLD = DK + 1;
+constexpr int DM = 128, DN = 128, DK = 16;
+// LDS row of an operand: 16-byte chunks stay aligned, and the 16 rows times two
+// k of a half-wave's fragment read cover every bank once.
+constexpr int DLD = DK + 2;
+typedef double d2 __attribute__((ext_vector_type(2)));
 
-// A operand loader variants for the FP64 kernels.
-struct LoadU64 {  // plain [M][K] rows
-  const double* a;
-  long lda;
-  __device__ void load(int m, int k0, int kq, double* v) const {
-    const double* p = a + (long)m * lda + k0 + kq;
+// Staging: thread t moves the 16-byte chunk t % 8 of the rows t / 8 + 32 q
+// (q < 4) of a 128 x 16 tile, so that a wave's load covers whole 128-byte rows.
+// The four row groups have uniform bases and one offset per thread; a group
+// past the last row repeats an earlier one (its products are not stored), so
+// no load is guarded and none waits for another.  Row counts are multiples
+// of 64.
+__device__ inline unsigned stage_offset(long ld) {
+  return (unsigned)((threadIdx.x >> 3) * ld + 2 * (threadIdx.x & 7));
+}
+__device__ inline d2 load_d2(const double* base, unsigned off) {
+  return *reinterpret_cast<const d2*>(base + off);
+}
+struct LoadRows64 {  // [rows][K]
+  const double* p[4];
+  unsigned off;
+  struct Raw {
+    d2 v[4];
+  };
+  __device__ LoadRows64(const double* a, long lda, int row0, int rows) : off(stage_offset(lda)) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = p[i];
+    for (int q = 0; q < 4; ++q) p[q] = a + (row0 + (row0 + 32 * q < rows ? 32 * q : 32 * (q & 1))) * lda;
   }
+  __device__ void load(int k0, Raw& r) const {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) r.v[q] = load_d2(p[q] + k0, off);
+  }
+  __device__ static d2 get(const Raw& r, int q) { return r.v[q]; }
 };
-struct LoadPsiV64 {  // A[(b,v)][r] = phi_v(r) V_b(r)
-  const double* psi_v_t;
-  const double* vpot;
-  long nrp;
-  int nvp;
-  __device__ void load(int m, int k0, int kq, double* v) const {
-    const int b = m / nvp, vv = m - b * nvp;
-    const double* p = psi_v_t + (long)vv * nrp + k0 + kq;
-    const double* q = vpot + (long)b * nrp + k0 + kq;
+// A[(b,v)][r] = phi_v(r) V_b(r): the factors stay apart until they are stored
+// (multiplied at the load, every K step waited for its own loads).  N_vp is a
+// multiple of 64: the row groups q and q + 1 (q even) share b.
+struct LoadPsiV64 {
+  const double *p[4], *v[2];
+  unsigned off, voff;
+  struct Raw {
+    d2 p[4], v[2];
+  };
+  __device__ LoadPsiV64(const double* psi_v_t, const double* vpot, long nrp, int nvp, int row0,
+                        int rows)
+      : off(stage_offset(nrp)), voff(2 * (threadIdx.x & 7)) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = p[i] * q[i];
+    for (int q = 0; q < 4; ++q) {
+      const int m = row0 + (row0 + 32 * q < rows ? 32 * q : 32 * (q & 1)), b = m / nvp;
+      p[q] = psi_v_t + (long)(m - b * nvp) * nrp;
+      if (q % 2 == 0) v[q / 2] = vpot + (long)b * nrp;
+    }
   }
+  __device__ void load(int k0, Raw& r) const {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) r.p[q] = load_d2(p[q] + k0, off);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) r.v[h] = load_d2(v[h] + k0, voff);
+  }
+  __device__ static d2 get(const Raw& r, int q) { return r.p[q] * r.v[q >> 1]; }
 };
 
-// Main loop of the FP64 kernels: acc += A[m0.., k] B[n0.., k] for k in [kb, ke).
+struct F64Smem {
+  double a[2][DM][DLD], b[2][DN][DLD];
+};
+
+// Instruction order of one K step (per wave 64 MFMAs in rows of 4, 32 fragment
+// reads, 8 or 10 global loads of the next step and 8 LDS stores), imposed on
+// the compiler's scheduler: the first fragments, then per row of MFMAs two
+// fragment reads of the next four k, the loads behind the first rows and the
+// stores behind the last eight.  64 coupling vectors, 64 + 256 orbitals, 48^3,
+// per call: 4.06 ms with one buffer and guarded loads, 3.77 with two buffers and
+// unguarded ones, 3.52 with this order but the stores in the last four rows, 3.44
+// as it is (67 TFLOP/s in the GEMM; rocBLAS's square 8,192 product 72), 3.60 with
+// the stores two rows earlier.
+template <int G>
+__device__ inline void f64_sched() {
+  if constexpr (G < 16) {
+    if constexpr (G == 0) __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);  // LDS reads
+    __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);                       // MFMA
+    if constexpr (G < 12) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+    if constexpr (G < 5) __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);   // global loads
+    if constexpr (G >= 8) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);  // LDS stores
+    f64_sched<G + 1>();
+  }
+}
+
+// Main loop of the FP64 kernels: acc += A[m0.., k] B[n0.., k] for k in
+// [kb, ke), an even number of steps.  Two LDS buffers, one barrier per step;
+// the next step's loads are in flight during the 64 matrix instructions (4,096
+// cycles) of the current one.
 template <typename LA>
-__device__ inline void f64_mainloop(const LA& la, int M, const double* __restrict__ bop, long ldb,
-                                    int nvalid, int m0, int n0, int kb, int ke, double (*As)[DLD],
-                                    double (*Bs)[DLD], d4 (&acc)[4][4]) {
+__device__ inline void f64_mainloop(const LA& la, const LoadRows64& lb, int kb, int ke, F64Smem& sm,
+                                    d4 (&acc)[4][4]) {
   const int t = threadIdx.x, l = t & 63, w = t >> 6;
   const int wm = w >> 1, wn = w & 1;
-  const int lrow = t >> 1, lkq = (t & 1) * 8;
-  double ra[8], rb[8];
-  const bool arow_ok = (m0 + lrow) < M;
+  const int row = t >> 3, col = 2 * (t & 7);
+  typename LA::Raw ra;
+  LoadRows64::Raw rb;
   auto gload = [&](int k0) {
-    if (arow_ok) {
-      la.load(m0 + lrow, k0, lkq, ra);
-    } else {
+    const int k = min(k0, ke - DK);
+    la.load(k, ra);
+    lb.load(k, rb);
+  };
+  auto lstore = [&](int buf) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) ra[i] = 0.0;
-    }
-    if (n0 + lrow < nvalid) {
-      const double* p = bop + (long)(n0 + lrow) * ldb + k0 + lkq;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) rb[i] = p[i];
-    } else {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) rb[i] = 0.0;
+    for (int q = 0; q < 4; ++q) {
+      *reinterpret_cast<d2*>(&sm.a[buf][row + 32 * q][col]) = LA::get(ra, q);
+      *reinterpret_cast<d2*>(&sm.b[buf][row + 32 * q][col]) = LoadRows64::get(rb, q);
     }
   };
-  auto lstore = [&]() {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      As[lrow][lkq + i] = ra[i];
-      Bs[lrow][lkq + i] = rb[i];
-    }
-  };
-  if (kb < ke) {
-    gload(kb);
-    lstore();
-  }
-  __syncthreads();
-  for (int k0 = kb; k0 < ke; k0 += DK) {
-    const bool more = k0 + DK < ke;
-    if (more) gload(k0 + DK);
+  auto mma = [&](int buf) {
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
       double a[4], b[4];
       const int kk = 4 * ks + (l >> 4);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        a[i] = As[wm * 64 + 16 * i + (l & 15)][kk];
-        b[i] = Bs[wn * 64 + 16 * i + (l & 15)][kk];
+        a[i] = sm.a[buf][wm * 64 + 16 * i + (l & 15)][kk];
+        b[i] = sm.b[buf][wn * 64 + 16 * i + (l & 15)][kk];
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i)
@@ -156,20 +201,34 @@ __device__ inline void f64_mainloop(const LA& la, int M, const double* __restric
         for (int j = 0; j < 4; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
     }
-    __syncthreads();
-    if (more) {
-      lstore();
-      __syncthreads();
-    }
+  };
+  if (kb < ke) {
+    gload(kb);
+    lstore(0);
   }
+  __syncthreads();
+  // (a raised priority in the loop: a block in its epilogue yields; 0.5 %)
+  __builtin_amdgcn_s_setprio(1);
+  for (int k0 = kb; k0 < ke; k0 += 2 * DK) {
+    gload(k0 + DK);
+    mma(0);
+    lstore(1);
+    f64_sched<0>();
+    __syncthreads();
+    gload(k0 + 2 * DK);
+    mma(1);
+    lstore(0);
+    f64_sched<0>();
+    __syncthreads();
+  }
+  __builtin_amdgcn_s_setprio(0);
 }
 
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 gemm1_f64m_kernel(GemmDims d, int M, int nb, const double* __restrict__ psi_c_rc,
                   const double* __restrict__ psi_v_rv, const double* __restrict__ u,
                   double* __restrict__ rho_part) {
-  __shared__ double As[DM][DLD];
-  __shared__ double Bs[DN][DLD];
+  __shared__ F64Smem sm;
   const int mt = (M + DM - 1) / DM, nt = d.nrp / DN;
   int mi, ni;
   if (!gemm1_tile(blockIdx.x, mt, nt, (long)DM * d.ncp * 8, mi, ni)) return;
@@ -179,8 +238,8 @@ gemm1_f64m_kernel(GemmDims d, int M, int nb, const double* __restrict__ psi_c_rc
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = d4{0, 0, 0, 0};
-  LoadU64 la{u, d.ncp};
-  f64_mainloop(la, M, psi_c_rc, d.ncp, d.nrp, m0, n0, 0, d.ncp, As, Bs, acc);
+  const LoadRows64 la(u, d.ncp, m0, M), lb(psi_c_rc, d.ncp, n0, d.nrp);
+  f64_mainloop(la, lb, 0, d.ncp, sm, acc);
   // epilogue: rho_b(r) = sum over the wave's 64 rows (one b, 64 v) of phi_v(r) C1
   const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int wm = w >> 1, wn = w & 1;
@@ -206,8 +265,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
 gemm2_f64m_kernel(GemmDims d, int M, int splitk, int kchunk, const double* __restrict__ psi_v_t,
                   const double* __restrict__ psi_c_t, const double* __restrict__ vpot,
                   double* __restrict__ ypart) {
-  __shared__ double As[DM][DLD];
-  __shared__ double Bs[DN][DLD];
+  __shared__ F64Smem sm;
   const int mt = (M + DM - 1) / DM, nt = (d.ncp + DN - 1) / DN;
   const int lid = xcd_remap(blockIdx.x, mt * nt * splitk);
   const int s = lid / (mt * nt);
@@ -220,8 +278,9 @@ gemm2_f64m_kernel(GemmDims d, int M, int splitk, int kchunk, const double* __res
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = d4{0, 0, 0, 0};
-  LoadPsiV64 la{psi_v_t, vpot, d.nrp, d.nvp};
-  f64_mainloop(la, M, psi_c_t, d.nrp, d.ncp, m0, n0, kb, ke, As, Bs, acc);
+  const LoadPsiV64 la(psi_v_t, vpot, d.nrp, d.nvp, m0, M);
+  const LoadRows64 lb(psi_c_t, d.nrp, n0, d.ncp);
+  f64_mainloop(la, lb, kb, ke, sm, acc);
   const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int wm = w >> 1, wn = w & 1;
   double* out = ypart + (long)s * M * d.ncp;
@@ -814,7 +873,7 @@ void gemm2_f64m(const GemmDims& d, int nb, int splitk, const double* psi_v_t,
                 const double* psi_c_t, const double* vpot, double* ypart, hipStream_t st) {
   if (nb <= 0) return;
   const int M = nb * d.nvp;
-  const int kchunk = (int)round_up(ceil_div(d.nrp, splitk), DK);
+  const int kchunk = (int)round_up(ceil_div(d.nrp, splitk), 2 * DK);
   const int blocks = ceil_div(M, DM) * ceil_div(d.ncp, DN) * splitk;
   gemm2_f64m_kernel<<<blocks, 256, 0, st>>>(d, M, splitk, kchunk, psi_v_t, psi_c_t, vpot, ypart);
   GWL_HIP(hipGetLastError());
