@@ -33,11 +33,12 @@ namespace gwl {
 namespace {
 
 typedef double d4 __attribute__((ext_vector_type(4)));
+typedef double d2 __attribute__((ext_vector_type(2)));
 
 constexpr int ZM = 128;       // rows: 2 occupied x 64 conduction indices
 constexpr int ZN = 128;       // columns: grid points
 constexpr int ZK = 16;        // K step
-constexpr int ZLD = ZM + 4;   // LDS row of one k (doubles)
+constexpr int ZLD = ZM + 16;  // LDS row of one k (doubles): two k rows fill all banks
 constexpr int NT = 256;
 
 __device__ inline int xcd_remap_z(int bid, int total) {
@@ -45,27 +46,44 @@ __device__ inline int xcd_remap_z(int bid, int total) {
   return (bid & 7) * (total >> 3) + (bid >> 3);
 }
 
+// Instruction order of one K step, as in the FP64 GEMMs: the first fragments,
+// then per row of four MFMAs two fragment reads of the next four k; the next
+// step's eight global loads behind the first rows, its eight LDS stores behind
+// the last.  (168 products, 64 + 256 orbitals, 48^3: 12.2 -> 11.9 ms with two
+// buffers, unguarded 16-byte loads and this order; the rest is the epilogue's
+// chains of loads and adds.)
+template <int G>
+__device__ inline void z_sched() {
+  if constexpr (G < 16) {
+    if constexpr (G == 0) __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);  // LDS reads
+    __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);                       // MFMA
+    if constexpr (G < 12) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+    if constexpr (G < 4) __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);   // global loads
+    if constexpr (G >= 8) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);  // LDS stores
+    z_sched<G + 1>();
+  }
+}
+
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 zgemm_kernel(GemmDims d, int nv, ZSeg s0, ZSeg s1, const double* __restrict__ psi_c_rc,
              const double* __restrict__ psi_v_rv, double dv, double* __restrict__ grad_c,
              double* __restrict__ gvpart) {
-  // one operand tile pair [ZK][ZLD] during the K loop; the exchange of the
+  // two operand tile pairs [ZK][ZLD] during the K loop; the exchange of the
   // occupied-gradient halves between the wave pairs after it
-  __shared__ double As[ZK][ZLD];
-  __shared__ double Bs[ZK][ZLD];
+  __shared__ double As[2][ZK][ZLD];
+  __shared__ double Bs[2][ZK][ZLD];
   __shared__ double xs[2][ZN];
   const int nct = d.ncp / 64, nrt = d.nrp / ZN;
   const int lid = xcd_remap_z(blockIdx.x, nct * nrt);
   const int rt = lid / nct, ct = lid - rt * nct;
   const int r0 = rt * ZN, c0 = ct * 64;
-  const int t = threadIdx.x, l = t & 63, w = t >> 6;
+  const int t = threadIdx.x, l = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wm = w >> 1, wn = w & 1;
   const int K = s0.k + s1.k;
-  // loader: k row lk of the step, 8 consecutive doubles at column lm
-  // (columns: 64 conduction indices of v0, then 64 of v0 + 1)
-  const int lk = t >> 4, lm = (t & 15) * 8;
-  const int lvo = lm >> 6, lc = c0 + (lm & 63);
+  // loader: wave w stages the k rows w + 4 q (q < 4), a lane two consecutive
+  // doubles (columns: 64 conduction indices of v0, then 64 of v0 + 1)
   const long ld_u = (long)d.nvp * d.ncp;
+  const unsigned uoff = (unsigned)((l >> 5) * d.ncp + 2 * (l & 31));
   // wave (wm, wn) computes Z for both v of the pair, conduction indices
   // c0 + 32 wm + [0, 32), grid points r0 + 64 wn + [0, 64): MFMA row block i
   // is v offset i >> 1, conduction offset 32 wm + 16 (i & 1)
@@ -73,64 +91,47 @@ zgemm_kernel(GemmDims d, int nv, ZSeg s0, ZSeg s1, const double* __restrict__ ps
 #pragma unroll
   for (int i = 0; i < 4; ++i) acol[i] = (i >> 1) * 64 + wm * 32 + 16 * (i & 1) + (l & 15);
 
+  d2 ra[4], rb[4];
+  // rows past the last product repeat it and are zeroed in A as they are
+  // stored (v0 + 1 < N_vp: N_vp is a multiple of 64, v0 is even, and padded
+  // rows are zero): no load is guarded
+  auto gload = [&](int v0, int k0) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int k = min(k0 + w + 4 * q, K - 1);
+      const bool first = k < s0.k;
+      const int ks = first ? k : k - s0.k;
+      const double* up = (first ? s0.u : s1.u) + (long)ks * ld_u + (long)v0 * d.ncp + c0;
+      const double* vp = (first ? s0.vf : s1.vf) + (long)ks * d.nrp + r0;
+      ra[q] = *reinterpret_cast<const d2*>(up + uoff);
+      rb[q] = *reinterpret_cast<const d2*>(vp + 2 * l);
+    }
+  };
+  auto lstore = [&](int buf, int k0) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int kr = w + 4 * q;
+      *reinterpret_cast<d2*>(&As[buf][kr][2 * l]) = k0 + kr < K ? ra[q] : d2{0.0, 0.0};
+      *reinterpret_cast<d2*>(&Bs[buf][kr][2 * l]) = rb[q];
+    }
+  };
+  const int steps = (K + ZK - 1) / ZK;
+  gload(0, 0);
   for (int v0 = 0; v0 < nv; v0 += 2) {
     d4 acc[4][4];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc[i][j] = d4{0, 0, 0, 0};
-    const int lv = v0 + lvo;
-    double ra[8], rb[8];
-    auto gload = [&](int k0) {
-      const int k = k0 + lk;
-      const double* up = nullptr;
-      const double* vp = nullptr;
-      if (k < s0.k) {
-        up = s0.u + (long)k * ld_u;
-        vp = s0.vf + (long)k * d.nrp;
-      } else if (k < K) {
-        up = s1.u + (long)(k - s0.k) * ld_u;
-        vp = s1.vf + (long)(k - s0.k) * d.nrp;
-      }
-      if (up && lv < nv) {
-        const double* p = up + (long)lv * d.ncp + lc;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) ra[i] = p[i];
-      } else {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) ra[i] = 0.0;
-      }
-      if (vp) {
-        const double* p = vp + r0 + lm;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) rb[i] = p[i];
-      } else {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) rb[i] = 0.0;
-      }
-    };
-    auto lstore = [&]() {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        As[lk][lm + i] = ra[i];
-        Bs[lk][lm + i] = rb[i];
-      }
-    };
-    gload(0);
-    __syncthreads();  // the previous pair's epilogue has read xs
-    lstore();
-    __syncthreads();
-    for (int k0 = 0; k0 < K; k0 += ZK) {
-      const bool more = k0 + ZK < K;
-      if (more) gload(k0 + ZK);
+    auto mma = [&](int buf) {
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) {
         const int kk = 4 * ks + (l >> 4);
         double a[4], b[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          a[i] = As[kk][acol[i]];
-          b[i] = Bs[kk][wn * 64 + 16 * i + (l & 15)];
+          a[i] = As[buf][kk][acol[i]];
+          b[i] = Bs[buf][kk][wn * 64 + 16 * i + (l & 15)];
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i)
@@ -138,11 +139,17 @@ zgemm_kernel(GemmDims d, int nv, ZSeg s0, ZSeg s1, const double* __restrict__ ps
           for (int j = 0; j < 4; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
       }
+    };
+    // (the loop ends with a barrier: the previous pair's tiles have been read)
+    lstore(0, 0);
+    __syncthreads();
+    for (int s = 0; s < steps; ++s) {
+      const int cur = s & 1;
+      gload(v0, (s + 1) * ZK);
+      mma(cur);
+      lstore(cur ^ 1, (s + 1) * ZK);
+      z_sched<0>();
       __syncthreads();
-      if (more) {
-        lstore();
-        __syncthreads();
-      }
     }
     // epilogue of the pair: acc[i][j][q] is Z at v = v0 + (i >> 1),
     // c = c0 + 32 wm + 16 (i & 1) + (l >> 4) + 4 q, r = r0 + 64 wn + 16 j + (l & 15).
@@ -180,6 +187,7 @@ zgemm_kernel(GemmDims d, int nv, ZSeg s0, ZSeg s1, const double* __restrict__ ps
       // accumulators would exceed the register budget of two waves per SIMD
       __builtin_amdgcn_sched_barrier(0);
     }
+    gload(min(v0 + 2, (nv - 1) & ~1), 0);  // the next pair's first step
     if (wm == 1 && l < 16) {
 #pragma unroll
       for (int vo = 0; vo < 2; ++vo)

@@ -35,8 +35,6 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 typedef double d2v __attribute__((ext_vector_type(2)));
 
 constexpr int NT = 256;
-constexpr int KB = 16;       // K step
-constexpr int ALD = KB + 1;  // LDS row of an operand stored row by row
 
 // M tiles: as few as hold the batch with at most 128 rows each, evenly filled.
 inline int pd_mt(int nb) { return (nb + 127) / 128; }
@@ -51,13 +49,27 @@ __device__ inline int pd_item(int bid, int total) {
 }
 inline int pd_grid(long total) { return (int)(8 * ((total + 7) / 8)); }
 
-// Block tile: 16 MI rows x NB columns, the wave's column block wc and its
-// share kg of the K step.
-template <int MI, int NJ, int KG>
+// Block tile: 16 MI rows x NB columns, KB deep (at most KMAX): the fewer matrix
+// instructions 16 of K take, the deeper the step, so that a barrier and a
+// load's latency are spread over enough of them, while two blocks fit a CU (one
+// C product of one vector, 24^3, 8 + 32 orbitals: 54.3 -> 50.1 us; 32-deep steps
+// gained nothing at 64 or 80 vectors).
+constexpr int pd_kb(int mi, int nj, int kg, int kmax) {
+  const int mt = 16 * mi, nb = 64 * nj / kg;
+  int kb = mi * nj <= 2 ? 64 : 16;
+  if (kb > kmax) kb = kmax;
+  while (kb > 16 && 16 * (mt * (kb + 2) + (nb + 16) * (kb + 2)) > 80 * 1024) kb /= 2;
+  return kb;
+}
+template <int MI, int NJ, int KG, int KMAX>
 struct PdTile {
   static_assert(KG == 1 || NJ == 1, "K shares only with one column block per wave");
   static constexpr int MT = 16 * MI, NB = 64 * NJ / KG;
   static constexpr int WC = 4 / KG;       // waves side by side
+  static constexpr int KB = pd_kb(MI, NJ, KG, KMAX);
+  // LDS row of an operand stored row by row: the 16 rows times two k of a
+  // half-wave's fragment read cover every bank once
+  static constexpr int ALD = KB + (MI > 2 ? 1 : 2);
   static constexpr int BLD1 = NB + 16;    // first GEMM: LDS row of the B tile [KB][BLD1]
   // two register stages (the loads of step s + 2 in flight while step s
   // computes and step s + 1 goes to LDS) up to the size of tile whose K step
@@ -67,19 +79,19 @@ struct PdTile {
 
 // acc += the wave's share of one K step.  a: row (l & 15) + 16 i, k = 4 ks +
 // (l >> 4) of [MT][ALD]; b: element (k, column) at k * brow + column * bcol.
-template <int MI, int NJ, int KG>
+template <typename T, int MI, int NJ, int KG>
 __device__ inline void pd_mma(const double* as, const double* bs, int bcol, int brow, int wc,
                               int kg, d4 (&acc)[MI][NJ]) {
   const int l = threadIdx.x & 63;
 #pragma unroll
-  for (int k4 = 0; k4 < KB / 4 / KG; ++k4) {
+  for (int k4 = 0; k4 < T::KB / 4 / KG; ++k4) {
     const int kk = 4 * (k4 * KG + kg) + (l >> 4);
     double b[NJ];
 #pragma unroll
     for (int j = 0; j < NJ; ++j) b[j] = bs[kk * brow + (16 * (wc * NJ + j) + (l & 15)) * bcol];
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
-      const double a = as[(16 * i + (l & 15)) * ALD + kk];
+      const double a = as[(16 * i + (l & 15)) * T::ALD + kk];
 #pragma unroll
       for (int j = 0; j < NJ; ++j)
         acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b[j], acc[i][j], 0, 0, 0);
@@ -88,7 +100,8 @@ __device__ inline void pd_mma(const double* as, const double* bs, int bcol, int 
 }
 
 // Sum of the KG shares into the waves of share 0 (the K loop has ended with a
-// barrier; sh is the block's staging memory, 512 MI doubles of it): the upper half of the shares hands over to the lower half.
+// barrier; sh is the block's staging memory, 512 MI doubles of it): the
+// upper half of the shares hands over to the lower half.
 template <int MI, int KG, int WC>
 __device__ inline void pd_reduce(double* sh, int wc, int kg, d4 (&acc)[MI][1]) {
   const int l = threadIdx.x & 63;
@@ -118,8 +131,9 @@ __global__ void __launch_bounds__(NT, 2)
 gemm1_pd_kernel(GemmDims d, long nvc, int nb, int mt, const double* __restrict__ psi_v_t,
                 const double* __restrict__ psi_c_t, const double* __restrict__ u,
                 double* __restrict__ rho) {
-  typedef PdTile<MI, NJ, KG> T;
-  constexpr int NB = T::NB, BLD = T::BLD1;
+  typedef PdTile<MI, NJ, KG, 32> T;  // (deeper ones than N_c would miss the path below)
+  constexpr int NB = T::NB, BLD = T::BLD1, KB = T::KB, ALD = T::ALD;
+  constexpr int AR = NT / KB, QA = T::MT / AR;  // A rows staged per pass, passes
   constexpr int SB = NB < 64 ? NB : 64;   // columns of a staged row segment
   constexpr int RK = KB * SB / NT;        // consecutive K rows staged by one thread
   constexpr int SA1 = T::MT * ALD, SB1 = KB * BLD;
@@ -137,8 +151,8 @@ gemm1_pd_kernel(GemmDims d, long nvc, int nb, int mt, const double* __restrict__
   for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < NJ; ++j) acc[i][j] = d4{0, 0, 0, 0};
-  // A: element e = t + 256 q of the tile is row e / 16, k = e % 16
-  const int ak = t & 15, ar = t >> 4;
+  // A: element e = t + 256 q of the tile is row e / KB, k = e % KB
+  const int ak = t % KB, ar = t / KB;
   // B: column t % SB (+ 64 j), K rows RK (t / SB) + [0, RK)
   const int bc = t % SB, br = KG == 1 ? RK * w : RK * (t / SB);
   // Every load is unconditional (a guarded one made the compiler wait for it
@@ -150,23 +164,23 @@ gemm1_pd_kernel(GemmDims d, long nvc, int nb, int mt, const double* __restrict__
   const double* const pcb = psi_c_t + n0 + bc;
   auto lstore_a = [&](int buf, const double* a, bool ok) {
 #pragma unroll
-    for (int q = 0; q < MI; ++q) As[buf * SA1 + (ar + 16 * q) * ALD + ak] = ok ? a[q] : 0.0;
+    for (int q = 0; q < QA; ++q) As[buf * SA1 + (ar + AR * q) * ALD + ak] = ok ? a[q] : 0.0;
   };
 
-  // Whole blocks of 16 conduction orbitals: a block's values stay in registers
+  // Whole blocks of KB conduction orbitals: a block's values stay in registers
   // while all occupied orbitals go by, so a K step reads one orbital row
-  // besides u (against 16; 396 -> 333 us at 32^3, 32 + 128 orbitals, 64 vectors).
+  // besides u (against KB; 396 -> 333 us at 32^3, 32 + 128 orbitals, 64 vectors).
   const int ncf = d.nv > 1 ? d.nc / KB * KB : 0;
   if (ncf > 0) {
     struct Stage {
-      double a[MI], v[NJ];
+      double a[QA], v[NJ];
     } x0, x1;
     double cn[RK][NJ], cc[RK][NJ];
     int v = 0, c0 = 0, lv = 0;  // next step to load, occupied orbital of the next to store
     auto gload = [&](Stage& x) {
       const double* p = ap + (long)v * d.nc + c0;
 #pragma unroll
-      for (int q = 0; q < MI; ++q) x.a[q] = p[16 * q * nvc];
+      for (int q = 0; q < QA; ++q) x.a[q] = p[AR * q * nvc];
 #pragma unroll
       for (int j = 0; j < NJ; ++j) x.v[j] = pvb[(long)v * d.nrp + 64 * j];
       if (v == 0) {
@@ -203,20 +217,20 @@ gemm1_pd_kernel(GemmDims d, long nvc, int nb, int mt, const double* __restrict__
     __syncthreads();
     for (int s = 0; s < steps; s += 2) {
       gload(x0);
-      pd_mma<MI, NJ, KG>(As, Bs, 1, BLD, wc, kg, acc);
+      pd_mma<T, MI, NJ, KG>(As, Bs, 1, BLD, wc, kg, acc);
       lstore(1, T::DEEP ? x1 : x0, s + 1 < steps);
       __syncthreads();
       gload(T::DEEP ? x1 : x0);
-      pd_mma<MI, NJ, KG>(As + SA1, Bs + SB1, 1, BLD, wc, kg, acc);
+      pd_mma<T, MI, NJ, KG>(As + SA1, Bs + SB1, 1, BLD, wc, kg, acc);
       lstore(0, x0, s + 2 < steps);
       __syncthreads();
     }
   }
-  // The remaining (fewer than 16) conduction orbitals, or all pairs when there
+  // The remaining (fewer than KB) conduction orbitals, or all pairs when there
   // is one occupied orbital: flat over (v, c), a K step may span several v.
   const int tw = d.nc - ncf;
   if (tw > 0) {
-    double xa[MI], xv[RK][NJ], xc[RK][NJ];
+    double xa[QA], xv[RK][NJ], xc[RK][NJ];
     const int nflat = d.nv * tw;
     const int dv = KB / tw, dc = KB - dv * tw;  // pair step of KB
     int av = ak / tw, ac = ak - av * tw;        // pair of the thread's A column
@@ -231,7 +245,7 @@ gemm1_pd_kernel(GemmDims d, long nvc, int nb, int mt, const double* __restrict__
     auto gload = [&]() {
       const double* p = ap - ak + (long)min(av, d.nv - 1) * d.nc + ncf + ac;
 #pragma unroll
-      for (int q = 0; q < MI; ++q) xa[q] = p[16 * q * nvc];
+      for (int q = 0; q < QA; ++q) xa[q] = p[AR * q * nvc];
       int vi = v, ci = c;
 #pragma unroll
       for (int i = 0; i < RK; ++i) {
@@ -263,7 +277,7 @@ gemm1_pd_kernel(GemmDims d, long nvc, int nb, int mt, const double* __restrict__
     for (int k0 = 0; k0 < nflat; k0 += KB) {
       const int cur = (k0 / KB) & 1;
       gload();
-      pd_mma<MI, NJ, KG>(As + cur * SA1, Bs + cur * SB1, 1, BLD, wc, kg, acc);
+      pd_mma<T, MI, NJ, KG>(As + cur * SA1, Bs + cur * SB1, 1, BLD, wc, kg, acc);
       lstore(cur ^ 1, k0 + KB);
       __syncthreads();
     }
@@ -289,11 +303,13 @@ __global__ void __launch_bounds__(NT, 2)
 gemm2_pd_kernel(GemmDims d, long nvc, int nb, int mt, int nt, int splitk, int kchunk,
                 const double* __restrict__ psi_v_t, const double* __restrict__ psi_c_t,
                 const double* __restrict__ vpot, double* __restrict__ ypart) {
-  typedef PdTile<MI, NJ, KG> T;
-  constexpr int NB = T::NB, MT = T::MT;
-  constexpr int QA = (MI + 3) / 4;         // 4-element chunks of the A tile per thread
-  constexpr int CW = KG == 1 ? 4 : 4 / KG;  // grid points of a thread's B chunk
-  constexpr int TR = KB / CW;              // threads per B row
+  typedef PdTile<MI, NJ, KG, 64> T;
+  constexpr int NB = T::NB, MT = T::MT, KB = T::KB, ALD = T::ALD;
+  // 4 grid points of a row per thread and pass (A), CW of them (B)
+  constexpr int AT = KB / 4, AR = NT / AT, QA = (MT + AR - 1) / AR;
+  constexpr int CW = NB * KB >= 4 * NT ? 4 : NB * KB / NT;
+  constexpr int BT = KB / CW, BR = NT / BT, QB = NB / BR;
+  static_assert(CW >= 1 && QB * BR == NB, "B staging");
   constexpr int SA1 = MT * ALD, SB1 = NB * ALD;
   __shared__ double sh[2 * (SA1 + SB1)];
   double* const As = sh;
@@ -310,13 +326,12 @@ gemm2_pd_kernel(GemmDims d, long nvc, int nb, int mt, int nt, int splitk, int kc
   for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < NJ; ++j) acc[i][j] = d4{0, 0, 0, 0};
-  // A: chunk t + 256 q of the tile is row (t >> 2) + 64 q, 4 grid points at 4 (t & 3)
-  const int row = t >> 2, col = 4 * (t & 3);
-  const int brow = t / TR, bcol = CW * (t % TR);
-  const double *pv[NJ], *pc[NJ];
+  const int row = t / AT, col = 4 * (t % AT);
+  const int brow = t / BT, bcol = CW * (t % BT);
+  const double *pv[QB], *pc[QB];
 #pragma unroll
-  for (int j = 0; j < NJ; ++j) {
-    const long n = min((long)n0 + brow + 64 * j, nvc - 1);  // (columns past the end: dropped)
+  for (int j = 0; j < QB; ++j) {
+    const long n = min((long)n0 + brow + BR * j, nvc - 1);  // (columns past the end: dropped)
     const int v = (int)(n / d.nc), c = (int)(n - (long)v * d.nc);
     pv[j] = psi_v_t + (long)v * d.nrp + bcol;
     pc[j] = psi_c_t + (long)c * d.nrp + bcol;
@@ -324,10 +339,10 @@ gemm2_pd_kernel(GemmDims d, long nvc, int nb, int mt, int nt, int splitk, int kc
   const double* pa[QA];
 #pragma unroll
   for (int q = 0; q < QA; ++q)
-    pa[q] = vpot + (long)min(m0 + row + 64 * q, nb - 1) * d.nrp + col;
+    pa[q] = vpot + (long)min(m0 + row + AR * q, nb - 1) * d.nrp + col;
   struct Stage {  // (loads unconditional: as in the first GEMM)
     d2v a[QA][2];
-    double v[NJ][CW], c[NJ][CW];
+    double v[QB][CW], c[QB][CW];
   } x0, x1;
   auto gload = [&](Stage& x, int k) {
     const int k0 = min(k, ke - KB);
@@ -336,7 +351,7 @@ gemm2_pd_kernel(GemmDims d, long nvc, int nb, int mt, int nt, int splitk, int kc
 #pragma unroll
       for (int h = 0; h < 2; ++h) x.a[q][h] = *reinterpret_cast<const d2v*>(pa[q] + k0 + 2 * h);
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
+    for (int j = 0; j < QB; ++j) {
       if constexpr (CW > 1) {
 #pragma unroll
         for (int h = 0; h < CW; h += 2) {
@@ -356,18 +371,18 @@ gemm2_pd_kernel(GemmDims d, long nvc, int nb, int mt, int nt, int splitk, int kc
   auto lstore = [&](int buf, const Stage& x) {
 #pragma unroll
     for (int q = 0; q < QA; ++q) {
-      const int m = row + 64 * q;
+      const int m = row + AR * q;
       if (m < MT)
 #pragma unroll
         for (int e = 0; e < 4; ++e) As[buf * SA1 + m * ALD + col + e] = x.a[q][e >> 1][e & 1];
     }
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
+    for (int j = 0; j < QB; ++j)
 #pragma unroll
       for (int e = 0; e < CW; ++e)
-        Bs[buf * SB1 + (brow + 64 * j) * ALD + bcol + e] = x.v[j][e] * x.c[j][e];
+        Bs[buf * SB1 + (brow + BR * j) * ALD + bcol + e] = x.v[j][e] * x.c[j][e];
   };
-  if (kb < ke) {  // (N_rp and kchunk are multiples of 2 KB)
+  if (kb < ke) {  // (N_rp and kchunk are multiples of 128)
     gload(x0, kb);
     if constexpr (T::DEEP) gload(x1, kb + KB);
     lstore(0, x0);
@@ -375,11 +390,11 @@ gemm2_pd_kernel(GemmDims d, long nvc, int nb, int mt, int nt, int splitk, int kc
   __syncthreads();
   for (int k0 = kb; k0 < ke; k0 += 2 * KB) {
     gload(x0, T::DEEP ? k0 + 2 * KB : k0 + KB);
-    pd_mma<MI, NJ, KG>(As, Bs, ALD, 1, wc, kg, acc);
+    pd_mma<T, MI, NJ, KG>(As, Bs, ALD, 1, wc, kg, acc);
     lstore(1, T::DEEP ? x1 : x0);
     __syncthreads();
     gload(T::DEEP ? x1 : x0, T::DEEP ? k0 + 3 * KB : k0 + 2 * KB);
-    pd_mma<MI, NJ, KG>(As + SA1, Bs + SB1, ALD, 1, wc, kg, acc);
+    pd_mma<T, MI, NJ, KG>(As + SA1, Bs + SB1, ALD, 1, wc, kg, acc);
     lstore(0, x0);
     __syncthreads();
   }
@@ -453,7 +468,7 @@ void gemm1_pd(const GemmDims& d, int nb, const double* psi_v_t, const double* ps
   const int mt = pd_mt(nb);
 #define GWL_PD(MIV, NJV, KGV)                                                              \
   gemm1_pd_kernel<MIV, NJV, KGV>                                                           \
-      <<<pd_grid((long)mt * (d.nrp / PdTile<MIV, NJV, KGV>::NB)), NT, 0, st>>>(            \
+      <<<pd_grid((long)mt * (d.nrp / (64 * NJV / KGV))), NT, 0, st>>>(            \
           d, nvc, nb, mt, psi_v_t, psi_c_t, u, rho)
   const long blocks = (long)mt * (d.nrp / 64);
   if (blocks >= 1024) {
@@ -474,10 +489,10 @@ void gemm2_pd(const GemmDims& d, int nb, int splitk, const double* psi_v_t,
   if (nb <= 0) return;
   const long nvc = (long)d.nv * d.nc;
   const int mt = pd_mt(nb);
-  const int kchunk = (int)round_up(ceil_div(d.nrp, splitk), 2 * KB);
+  const int kchunk = (int)round_up(ceil_div(d.nrp, splitk), 128);
 #define GWL_PD(MIV, NJV, KGV)                                                              \
   do {                                                                                     \
-    const int nt = ceil_div(nvc, PdTile<MIV, NJV, KGV>::NB);                               \
+    const int nt = ceil_div(nvc, (64 * NJV / KGV));                               \
     gemm2_pd_kernel<MIV, NJV, KGV><<<pd_grid((long)mt * nt * splitk), NT, 0, st>>>(        \
         d, nvc, nb, mt, nt, splitk, kchunk, psi_v_t, psi_c_t, vpot, ypart);                \
   } while (0)
