@@ -15,15 +15,21 @@ namespace {
 
 constexpr int CF_MAXL = 4000;
 
+// Bound by the chain of dependent FP64 divisions: the LDS holds the pair's
+// ld coefficients, not the longest recurrence's 4,000 (64 KB: two blocks per
+// CU), so that eight blocks hide each other's chains, and the real fraction
+// R(0) is wave 0's affair while the other waves are under way (640 pairs x 2,000
+// frequencies, L up to 200: 244 -> 173 us).
 __global__ void __launch_bounds__(256)
 cfrac_kernel(const double* __restrict__ ca, const double* __restrict__ cb,
              const int* __restrict__ lens, const double* __restrict__ norm2, int ld,
              const double* __restrict__ e_n, const double* __restrict__ eta_n,
              const double* __restrict__ omega, int nomega, double delta, int tda,
              double* __restrict__ sig) {
-  __shared__ double sa[CF_MAXL];
-  __shared__ double sb2[CF_MAXL];
+  extern __shared__ double coef[];
   __shared__ double r0_sh;
+  double* const sa = coef;
+  double* const sb2 = coef + ld;
   const int p = blockIdx.y;
   const int L = lens[p];
   const double n2 = norm2[p];
@@ -33,48 +39,53 @@ cfrac_kernel(const double* __restrict__ ca, const double* __restrict__ cb,
     sb2[k] = b * b;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  const bool run = L > 0 && n2 > 0.0;
+  if (threadIdx.x < 64) {
     double r0 = 0.0;
-    if (L > 0 && n2 > 0.0) {
+    if (run && !tda) {
       double t = -sa[L - 1];
       for (int k = L - 2; k >= 0; --k) t = -sa[k] - sb2[k] / t;
       r0 = n2 / t;
     }
-    r0_sh = r0;
+    if (threadIdx.x == 0) r0_sh = r0;
+  }
+  const double en = e_n[p], eta = eta_n[p];
+  const int w = blockIdx.x * blockDim.x + threadIdx.x;  // (one frequency per thread)
+  const double om = omega[w < nomega ? w : 0];
+  const double zr = om - en, zi = -eta * delta;
+  double rr = 0.0, ri = 0.0;
+  if (run) {
+    // zeta = -eta z
+    const double xr = -eta * zr, xi = -eta * zi;
+    double tr = xr - sa[L - 1], ti = xi;
+    for (int k = L - 2; k >= 0; --k) {
+      const double inv = sb2[k] / (tr * tr + ti * ti);
+      // t = zeta - a_k - b^2 / t ;  b^2 / t = b^2 conj(t) / |t|^2
+      tr = xr - sa[k] - inv * tr;
+      ti = xi + inv * ti;
+    }
+    // R(zeta) = n2 / t
+    const double d = 1.0 / (tr * tr + ti * ti);
+    rr = n2 * tr * d;
+    ri = -n2 * ti * d;
   }
   __syncthreads();
-  const double r0 = r0_sh;
-  const double en = e_n[p], eta = eta_n[p];
-  for (int w = blockIdx.x * blockDim.x + threadIdx.x; w < nomega; w += gridDim.x * blockDim.x) {
-    double sr = 0.0, si = 0.0;
-    if (L > 0 && n2 > 0.0) {
-      const double zr = omega[w] - en, zi = -eta * delta;
-      // zeta = -eta z
-      const double xr = -eta * zr, xi = -eta * zi;
-      double tr = xr - sa[L - 1], ti = xi;
-      for (int k = L - 2; k >= 0; --k) {
-        const double inv = sb2[k] / (tr * tr + ti * ti);
-        // t = zeta - a_k - b^2 / t ;  b^2 / t = b^2 conj(t) / |t|^2
-        tr = xr - sa[k] - inv * tr;
-        ti = xi + inv * ti;
-      }
-      // R(zeta) = n2 / t
-      const double d = 1.0 / (tr * tr + ti * ti);
-      const double rr = n2 * tr * d, ri = -n2 * ti * d;
-      if (tda) {
-        sr = -eta * rr;
-        si = -eta * ri;
-      } else {
-        // (R - r0) / z
-        const double nr = rr - r0, ni = ri;
-        const double dz = 1.0 / (zr * zr + zi * zi);
-        sr = (nr * zr + ni * zi) * dz;
-        si = (ni * zr - nr * zi) * dz;
-      }
+  if (w >= nomega) return;
+  double sr = 0.0, si = 0.0;
+  if (run) {
+    if (tda) {
+      sr = -eta * rr;
+      si = -eta * ri;
+    } else {
+      // (R - r0) / z
+      const double nr = rr - r0_sh, ni = ri;
+      const double dz = 1.0 / (zr * zr + zi * zi);
+      sr = (nr * zr + ni * zi) * dz;
+      si = (ni * zr - nr * zi) * dz;
     }
-    sig[((long)p * nomega + w) * 2] = sr * kHartreeEv;
-    sig[((long)p * nomega + w) * 2 + 1] = si * kHartreeEv;
   }
+  double2* const o = reinterpret_cast<double2*>(sig) + (long)p * nomega + w;
+  *o = double2{sr * kHartreeEv, si * kHartreeEv};
 }
 
 // ---------------------------------------------------------------- interval check
@@ -112,9 +123,19 @@ interval_check_kernel(int npairs, const double* __restrict__ ca, const double* _
 // tridiagonal T and the first components u_k(0) of its eigenvectors, by the
 // implicit QL iteration with shifts (Bowdler, Martin, Reinsch and Wilkinson)
 // applying each plane rotation to the first row of the eigenvector matrix
-// only (Golub and Welsch).  One thread per pair; d, e, z are that pair's rows
-// of the scratch arrays (FP64).  On return d = theta, z = ||P||^2 u(0)^2.
+// only (Golub and Welsch).  One thread per pair: a serial chain of rotations
+// over d, e and z (FP64), which live in LDS ([k][thread], stride = blockDim.x)
+// where 3 ld doubles for a useful number of threads fit there, and in the pair's
+// rows of the scratch arrays otherwise (80 pairs, L = 30: 1,257 us in the
+// scratch rows with 64 lanes per wave, 617 us as it is).  On return qd = theta, qz = ||P||^2 u(0)^2.
 // status[p] = 1 if an eigenvalue needed more than 60 sweeps.
+template <typename T>
+struct Strided {
+  T* p;
+  int s;
+  __device__ T& operator[](int i) const { return p[(long)i * s]; }
+};
+template <bool LDS>
 __global__ void quad_eig_kernel(int npairs, const double* __restrict__ ca,
                                 const double* __restrict__ cb, const int* __restrict__ lens,
                                 const double* __restrict__ norm2, int ld, double* __restrict__ qd,
@@ -123,9 +144,18 @@ __global__ void quad_eig_kernel(int npairs, const double* __restrict__ ca,
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= npairs) return;
   const int n = lens[p];
-  double* d = qd + (long)p * ld;
-  double* e = qe + (long)p * ld;
-  double* z = qz + (long)p * ld;
+  extern __shared__ double tri[];
+  const int s = LDS ? (int)blockDim.x : 1;
+  Strided<double> d, e, z;
+  if constexpr (LDS) {
+    d = {tri + threadIdx.x, s};
+    e = {d.p + (long)ld * s, s};
+    z = {e.p + (long)ld * s, s};
+  } else {
+    d = {qd + (long)p * ld, s};
+    e = {qe + (long)p * ld, s};
+    z = {qz + (long)p * ld, s};
+  }
   for (int i = 0; i < n; ++i) {
     d[i] = ca[(long)p * ld + i];
     e[i] = (i + 1 < n) ? cb[(long)p * ld + i] : 0.0;  // e[i] couples i and i + 1
@@ -149,11 +179,11 @@ __global__ void quad_eig_kernel(int npairs, const double* __restrict__ ca,
       double g = (d[l + 1] - d[l]) / (2.0 * e[l]);
       double r = hypot(g, 1.0);
       g = d[m] - d[l] + e[l] / (g + (g >= 0.0 ? r : -r));
-      double s = 1.0, c = 1.0, pp = 0.0;
+      double sn = 1.0, c = 1.0, pp = 0.0;
       int i = m - 1;
       bool underflow = false;
       for (; i >= l; --i) {
-        const double f = s * e[i], b = c * e[i];
+        const double f = sn * e[i], b = c * e[i];
         r = hypot(f, g);
         e[i + 1] = r;
         if (r == 0.0) {
@@ -162,16 +192,16 @@ __global__ void quad_eig_kernel(int npairs, const double* __restrict__ ca,
           underflow = true;
           break;
         }
-        s = f / r;
+        sn = f / r;
         c = g / r;
         g = d[i + 1] - pp;
-        r = (d[i] - g) * s + 2.0 * c * b;
-        pp = s * r;
+        r = (d[i] - g) * sn + 2.0 * c * b;
+        pp = sn * r;
         d[i + 1] = g + pp;
         g = c * r - b;
         const double zf = z[i + 1];
-        z[i + 1] = s * z[i] + c * zf;
-        z[i] = c * z[i] - s * zf;
+        z[i + 1] = sn * z[i] + c * zf;
+        z[i] = c * z[i] - sn * zf;
       }
       if (underflow) continue;
       d[l] -= pp;
@@ -180,7 +210,11 @@ __global__ void quad_eig_kernel(int npairs, const double* __restrict__ ca,
     }
   }
   const double n2 = norm2[p];
-  for (int i = 0; i < n; ++i) z[i] = n2 * z[i] * z[i];
+  for (int i = 0; i < n; ++i) {
+    const double w = n2 * z[i] * z[i];
+    qz[(long)p * ld + i] = w;
+    if constexpr (LDS) qd[(long)p * ld + i] = d[i];
+  }
   status[p] = bad;
 }
 
@@ -190,8 +224,9 @@ quad_sigma_kernel(const double* __restrict__ qd, const double* __restrict__ qz,
                   const int* __restrict__ lens, int ld, const double* __restrict__ e_n,
                   const double* __restrict__ eta_n, const double* __restrict__ omega, int nomega,
                   double delta, double* __restrict__ sig) {
-  __shared__ double so[CF_MAXL];
-  __shared__ double sw[CF_MAXL];
+  extern __shared__ double coef[];  // (as many as ld: see cfrac_kernel)
+  double* const so = coef;
+  double* const sw = coef + ld;
   const int p = blockIdx.y;
   const int L = lens[p];
   for (int k = threadIdx.x; k < L; k += blockDim.x) {
@@ -251,7 +286,7 @@ void cfrac_sigma(int npairs, const double* coef_a, const double* coef_b, const i
   if (npairs <= 0 || nomega <= 0) return;
   GWL_CHECK(ld <= CF_MAXL, GWL_EINVAL, "Lanczos length exceeds 4000");
   dim3 grid(ceil_div(nomega, 256), npairs);
-  cfrac_kernel<<<grid, 256, 0, st>>>(coef_a, coef_b, lens, norm2, ld, e_n, eta_n, omega_ha,
+  cfrac_kernel<<<grid, 256, 2 * sizeof(double) * ld, st>>>(coef_a, coef_b, lens, norm2, ld, e_n, eta_n, omega_ha,
                                      nomega, delta_ha, tda, sig);
   GWL_HIP(hipGetLastError());
 }
@@ -262,11 +297,21 @@ void quad_sigma(int npairs, const double* coef_a, const double* coef_b, const in
                 double* qz, int* status, double* sig, hipStream_t st) {
   if (npairs <= 0 || nomega <= 0) return;
   GWL_CHECK(ld <= CF_MAXL, GWL_EINVAL, "Lanczos length exceeds 4000");
-  quad_eig_kernel<<<ceil_div(npairs, 64), 64, 0, st>>>(npairs, coef_a, coef_b, lens, norm2, ld,
-                                                        qd, qe, qz, status);
+  // threads per block: one while a wave per SIMD is not reached (lanes of a wave
+  // wait for the longest of their sweeps), and no more than fit 64 KB of LDS
+  int nt = 1;
+  while (nt < 64 && ceil_div(npairs, nt) > 1024) nt *= 2;
+  while (nt > 1 && (size_t)nt * 3 * ld * sizeof(double) > 65536) nt /= 2;
+  const size_t lds = (size_t)nt * 3 * ld * sizeof(double);
+  if (lds <= 65536)
+    quad_eig_kernel<true><<<ceil_div(npairs, nt), nt, lds, st>>>(npairs, coef_a, coef_b, lens,
+                                                                 norm2, ld, qd, qe, qz, status);
+  else
+    quad_eig_kernel<false><<<ceil_div(npairs, 64), 64, 0, st>>>(npairs, coef_a, coef_b, lens, norm2,
+                                                                ld, qd, qe, qz, status);
   GWL_HIP(hipGetLastError());
   dim3 grid(ceil_div(nomega, 256), npairs);
-  quad_sigma_kernel<<<grid, 256, 0, st>>>(qd, qz, lens, ld, e_n, eta_n, omega_ha, nomega,
+  quad_sigma_kernel<<<grid, 256, 2 * sizeof(double) * ld, st>>>(qd, qz, lens, ld, e_n, eta_n, omega_ha, nomega,
                                           delta_ha, sig);
   GWL_HIP(hipGetLastError());
 }
