@@ -115,6 +115,12 @@ def _f64(a) -> np.ndarray:
     return np.ascontiguousarray(np.asarray(a, dtype=np.float64))
 
 
+def _complex(a: np.ndarray) -> np.ndarray:
+    """(re, im) pairs in the last axis, as the library writes them, seen as
+    complex128 (no copy: a sum of the two halves costs more than the call)."""
+    return a.view(np.complex128)[..., 0]
+
+
 def _ptr(a: np.ndarray):
     return a.ctypes.data_as(ct.c_void_p)
 
@@ -289,30 +295,30 @@ class Context:
         """Sigma^corr_mm(omega) in eV, complex128 [n_qp, n_omega]."""
         q = _i32(qp_states)
         om = _f64(omega_ev)
-        out = np.zeros((len(q), len(om), 2), dtype=np.float64)
+        out = np.empty((len(q), len(om), 2))
         _check(lib().gwl_sigma_c(self._h, _ptr(q), len(q), _ptr(om), len(om), float(eta_ev),
                                  int(n_lanczos), _ptr(out)))
-        return out[..., 0] + 1j * out[..., 1]
+        return _complex(out)
 
     def sigma_c_offdiag(self, m: int, m2: int, omega_ev, eta_ev: float,
                         n_lanczos: int) -> np.ndarray:
         """Off-diagonal Sigma^corr_mm2(omega) in eV, complex128 [n_omega]."""
         om = _f64(omega_ev)
-        out = np.zeros((len(om), 2), dtype=np.float64)
+        out = np.empty((len(om), 2))
         _check(lib().gwl_sigma_c_offdiag(self._h, int(m), int(m2), _ptr(om), len(om),
                                          float(eta_ev), int(n_lanczos), _ptr(out)))
-        return out[:, 0] + 1j * out[:, 1]
+        return _complex(out)
 
     def sigma_c_range(self, qp_states, n_begin: int, n_end: int, omega_ev, eta_ev: float,
                       n_lanczos: int) -> np.ndarray:
         """Sum of Sigma_mm(omega, n) over n in [n_begin, n_end), eV, [n_qp, n_omega]."""
         q = _i32(qp_states)
         om = _f64(omega_ev)
-        out = np.zeros((len(q), len(om), 2), dtype=np.float64)
+        out = np.empty((len(q), len(om), 2))
         _check(lib().gwl_sigma_c_range(self._h, _ptr(q), len(q), int(n_begin), int(n_end),
                                        _ptr(om), len(om), float(eta_ev), int(n_lanczos),
                                        _ptr(out)))
-        return out[..., 0] + 1j * out[..., 1]
+        return _complex(out)
 
     def sigma_c_vjp(self, qp_states, omega_ev, eta_ev: float, n_lanczos: int, grad_sigma,
                     device="cuda", n_range=None):
@@ -326,7 +332,7 @@ class Context:
         om = _f64(omega_ev)
         G = np.asarray(grad_sigma, dtype=np.complex128).reshape(len(q), len(om))
         g2 = np.ascontiguousarray(np.stack([G.real, G.imag], axis=-1))
-        sig = np.zeros((len(q), len(om), 2))
+        sig = np.empty((len(q), len(om), 2))
         ge = np.zeros(self.n_orb)
         gdt = torch.float64 if self.orb_itemsize == 8 else torch.float32
         go = torch.empty((self.n_orb, self.n_r), dtype=gdt, device=device)
@@ -340,7 +346,7 @@ class Context:
                                                int(n_range[1]), _ptr(om), len(om),
                                                float(eta_ev), int(n_lanczos), _ptr(g2),
                                                _ptr(sig), _ptr(ge), _dev(go, gdt)))
-        return sig[..., 0] + 1j * sig[..., 1], ge, go
+        return _complex(sig), ge, go
 
     def sigma_c_vjp_forward(self, qp_states, omega_ev, eta_ev: float, n_lanczos: int,
                             n_range=None):
@@ -350,12 +356,12 @@ class Context:
         q = _i32(qp_states)
         om = _f64(omega_ev)
         n0, n1 = (0, self.n_orb) if n_range is None else (int(n_range[0]), int(n_range[1]))
-        sig = np.zeros((len(q), len(om), 2))
+        sig = np.empty((len(q), len(om), 2))
         _sync_torch()
         _check(lib().gwl_sigma_c_vjp_forward(self._h, _ptr(q), len(q), n0, n1, _ptr(om),
                                              len(om), float(eta_ev), int(n_lanczos), _ptr(sig)))
         self._vjp_shape = (len(q), len(om))
-        return sig[..., 0] + 1j * sig[..., 1]
+        return _complex(sig)
 
     def sigma_c_vjp_backward(self, grad_sigma, device="cuda"):
         """(dl/d energies [n_orb] per eV, dl/d orbitals [n_orb, N_r] on the
@@ -392,11 +398,11 @@ class Context:
         a, b, n2 = _f64(alpha), _f64(beta), _f64(norm2)
         ln = _i32(lens)
         om = _f64(omega_ev)
-        out = np.zeros((len(n), len(om), 2))
+        out = np.empty((len(n), len(om), 2))
         _check(lib().gwl_sigma_from_coeffs(self._h, _ptr(n), len(n), _ptr(a), _ptr(b), _ptr(n2),
                                            _ptr(ln), a.shape[1], _ptr(om), len(om), float(eta_ev),
                                            _ptr(out)))
-        return out[..., 0] + 1j * out[..., 1]
+        return _complex(out)
 
     def sigma_from_coeffs_noalloc(self, n_idx, alpha, beta, norm2, lens, omega_ev, eta_ev):
         """As sigma_from_coeffs, through the entry point that allocates no
@@ -405,11 +411,11 @@ class Context:
         a, b, n2 = _f64(alpha), _f64(beta), _f64(norm2)
         ln = _i32(lens)
         om = _f64(omega_ev)
-        out = np.zeros((len(n), len(om), 2))
+        out = np.empty((len(n), len(om), 2))
         _check(lib().gwl_sigma_from_coeffs_noalloc(self._h, _ptr(n), len(n), _ptr(a), _ptr(b),
                                                    _ptr(n2), _ptr(ln), a.shape[1], _ptr(om),
                                                    len(om), float(eta_ev), _ptr(out)))
-        return out[..., 0] + 1j * out[..., 1]
+        return _complex(out)
 
     # -- components (device tensors) ----------------------------------------
     def poisson(self, rho, precision: str = "fp64"):

@@ -32,7 +32,8 @@ struct DevBuf {
     n = 0;
   }
   // (Re)allocate to at least cnt elements, zero-filled.  Contents are not kept.
-  void ensure(size_t cnt) {
+  // sync = false: the caller waits for the fill.
+  void ensure(size_t cnt, bool sync = true) {
     if (cnt <= n) return;
     release();
     if (cnt == 0) return;
@@ -44,7 +45,13 @@ struct DevBuf {
     }
     n = cnt;
     GWL_HIP(hipMemset(p, 0, cnt * sizeof(T)));
-    GWL_HIP(hipDeviceSynchronize());
+    if (sync) GWL_HIP(hipDeviceSynchronize());
+  }
+  // At least cnt elements, the first cnt zero once the stream gets there.
+  void ensure_zero(size_t cnt, hipStream_t st) {
+    const bool kept = cnt <= n;
+    ensure(cnt);
+    if (kept && cnt) GWL_HIP(hipMemsetAsync(p, 0, cnt * sizeof(T), st));
   }
 };
 
@@ -141,6 +148,12 @@ struct gwl_ctx {
   int orb_dtype = 8;         // 8 = FP64 orbitals were given, 4 = FP32
   int adjoint_stored = -1;   // what the last adjoint call did (-1: no call yet)
   std::shared_ptr<void> vjp_saved;  // state of the last gwl_sigma_c_vjp_forward
+  std::shared_ptr<void> vjp_work;   // buffers of the last VJP call, if small (vjp.hip)
+  DevBuf<double> norms;             // row norms of caller-given vectors
+  // Pinned staging of large results (two chunks, made on first use)
+  static constexpr size_t kPinChunk = 2u << 20;
+  unsigned char* pin = nullptr;
+  hipEvent_t pin_ev[2] = {nullptr, nullptr};
   bool poly_hi_auto = false;  // the interval's upper end is estimated (re-done for ISDF)
   double hi_resid = 0.0;      // residual bound of the last estimate's largest Ritz value
   DevBuf<int> ivbad;          // per-run flags of the interval check
@@ -392,35 +405,36 @@ struct gwl_ctx {
     const long nvpc = (long)gd.nvp * gd.ncp;
     if (nb > cap) {
       ++work_gen;
-      q.ensure((size_t)nb * nvc);
-      qprev.ensure((size_t)nb * nvc);
-      w.ensure((size_t)nb * nvc);
-      ta.ensure((size_t)nb * nvc);
-      tb.ensure((size_t)nb * nvc);
-      u64.ensure((size_t)nb * nvpc);
-      u64c.ensure(gemm_pd_u_size(nb, nvc));
-      u16.ensure((size_t)alloc_rows_u(nb, gd.nvp) * gd.ncp);
-      rho.ensure((size_t)nvt_max() * nb * gd.nrp * 8);
-      vpot64.ensure((size_t)nb * gd.nrp);
-      vpot32.ensure((size_t)alloc_rows_v(nb, gd.nvp) * gd.nrp);
-      vpot16.ensure((size_t)alloc_rows_v(nb, gd.nvp) * gd.nrp);
-      xmax32.ensure((size_t)alloc_rows_v(nb, gd.nvp));
-      vexp32.ensure((size_t)alloc_rows_v(nb, gd.nvp));
-      fftx.ensure((size_t)((nb + 1) / 2) * nr * 16);
-      ypart.ensure(split_rows(nb) * nvpc * 8);
-      s_pair.ensure(nb);
-      s_k.ensure(nb);
-      s_len.ensure(nb);
-      s_dead.ensure(nb);
-      s_slots.ensure(nb);
-      s_act.ensure(nb);
-      s_m.ensure(nb);
-      s_n.ensure(nb);
-      s_amax.ensure(nb);
-      s_bprev.ensure(nb);
-      rw_n0.ensure(nb);
-      rw_part.ensure((size_t)nb * reorth_part_len(nvc));
-      rw_skip.ensure(nb);
+      q.ensure((size_t)nb * nvc, false);
+      qprev.ensure((size_t)nb * nvc, false);
+      w.ensure((size_t)nb * nvc, false);
+      ta.ensure((size_t)nb * nvc, false);
+      tb.ensure((size_t)nb * nvc, false);
+      u64.ensure((size_t)nb * nvpc, false);
+      u64c.ensure(gemm_pd_u_size(nb, nvc), false);
+      u16.ensure((size_t)alloc_rows_u(nb, gd.nvp) * gd.ncp, false);
+      rho.ensure((size_t)nvt_max() * nb * gd.nrp * 8, false);
+      vpot64.ensure((size_t)nb * gd.nrp, false);
+      vpot32.ensure((size_t)alloc_rows_v(nb, gd.nvp) * gd.nrp, false);
+      vpot16.ensure((size_t)alloc_rows_v(nb, gd.nvp) * gd.nrp, false);
+      xmax32.ensure((size_t)alloc_rows_v(nb, gd.nvp), false);
+      vexp32.ensure((size_t)alloc_rows_v(nb, gd.nvp), false);
+      fftx.ensure((size_t)((nb + 1) / 2) * nr * 16, false);
+      ypart.ensure(split_rows(nb) * nvpc * 8, false);
+      s_pair.ensure(nb, false);
+      s_k.ensure(nb, false);
+      s_len.ensure(nb, false);
+      s_dead.ensure(nb, false);
+      s_slots.ensure(nb, false);
+      s_act.ensure(nb, false);
+      s_m.ensure(nb, false);
+      s_n.ensure(nb, false);
+      s_amax.ensure(nb, false);
+      s_bprev.ensure(nb, false);
+      rw_n0.ensure(nb, false);
+      rw_part.ensure((size_t)nb * reorth_part_len(nvc), false);
+      rw_skip.ensure(nb, false);
+      GWL_HIP(hipDeviceSynchronize());  // one wait for all the fills
       cap = nb;
     }
     if (Lrows + 1 > cap_L || nb * (size_t)(Lrows + 1) > hbuf.n) {
@@ -428,6 +442,13 @@ struct gwl_ctx {
       cap_L = std::max(cap_L, Lrows + 1);
     }
     if (need_basis) basis.ensure((size_t)nb * Lrows * nvc);
+  }
+
+  // the Poisson scratch alone, for nf fields
+  void ensure_fft(int nf) {
+    const size_t need = (size_t)((nf + 1) / 2) * nr * 16;
+    if (need > fftx.n) ++work_gen;  // (captured graphs hold its address)
+    fftx.ensure(need);
   }
 
   int orb_row(int n) const { return n < nv ? n : gd.nvp + (n - nv); }

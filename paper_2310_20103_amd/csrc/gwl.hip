@@ -88,7 +88,7 @@ namespace {
 // Largest 2-norm among n_vec device vectors of length N_vc (sets the FP16
 // operand scale for caller-given vectors).
 double max_row_norm(gwl_ctx* ctx, const double* x, int n_vec) {
-  DevBuf<double> nrm;
+  DevBuf<double>& nrm = ctx->norms;
   nrm.ensure(n_vec);
   row_norm2(x, ctx->nvc, n_vec, nrm.p, ctx->stream);
   std::vector<double> h(n_vec);
@@ -101,6 +101,53 @@ double max_row_norm(gwl_ctx* ctx, const double* x, int n_vec) {
     m = std::max(m, v);
   }
   return m;
+}
+
+// Device result to the caller's host memory, complete on return.  A copy into
+// pageable memory goes through the runtime's own staging (20 MB: 1.1 ms); large
+// ones go chunk by chunk through two pinned buffers instead, one filling while
+// the host copies the other out (0.7 ms, most of it the page faults of fresh
+// memory).  Memory that is pinned already is written directly.
+void copy_out(gwl_ctx* ctx, void* dst, const void* src, size_t bytes) {
+  hipStream_t st = ctx->stream;
+  constexpr size_t chunk = gwl_ctx::kPinChunk;
+  bool staged = bytes >= 2 * chunk;
+  if (staged) {
+    hipPointerAttribute_t at;
+    if (hipPointerGetAttributes(&at, dst) == hipSuccess)
+      staged = at.type != hipMemoryTypeHost;
+    else
+      (void)hipGetLastError();  // (ordinary memory, to some versions)
+  }
+  if (staged && !ctx->pin) {
+    if (hipHostMalloc((void**)&ctx->pin, 2 * chunk, hipHostMallocDefault) == hipSuccess) {
+      for (auto& e : ctx->pin_ev)
+        if (!e) GWL_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    } else {
+      (void)hipGetLastError();
+      ctx->pin = nullptr;
+      staged = false;
+    }
+  }
+  if (!staged) {
+    GWL_HIP(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, st));
+    GWL_HIP(hipStreamSynchronize(st));
+    return;
+  }
+  const size_t n = (bytes + chunk - 1) / chunk;
+  auto size = [&](size_t i) { return std::min(chunk, bytes - i * chunk); };
+  for (size_t i = 0; i <= n; ++i) {
+    if (i < n) {
+      GWL_HIP(hipMemcpyAsync(ctx->pin + (i & 1) * chunk, static_cast<const char*>(src) + i * chunk,
+                             size(i), hipMemcpyDeviceToHost, st));
+      GWL_HIP(hipEventRecord(ctx->pin_ev[i & 1], st));
+    }
+    if (i > 0) {
+      GWL_HIP(hipEventSynchronize(ctx->pin_ev[(i - 1) & 1]));
+      std::memcpy(static_cast<char*>(dst) + (i - 1) * chunk, ctx->pin + ((i - 1) & 1) * chunk,
+                  size(i - 1));
+    }
+  }
 }
 
 // Potentials of the caller into the padded [nb][N_rp] rows of the FP64 product
@@ -391,6 +438,9 @@ void gwl_destroy(gwl_ctx* ctx) {
   for (auto e : ctx->ev_pool) (void)hipEventDestroy(e);
   ctx->drop_graph();
   if (ctx->blas) (void)rocblas_destroy_handle(static_cast<rocblas_handle>(ctx->blas));
+  if (ctx->pin) (void)hipHostFree(ctx->pin);
+  for (auto e : ctx->pin_ev)
+    if (e) (void)hipEventDestroy(e);
   if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);
   delete ctx;
 }
@@ -516,7 +566,7 @@ gwl_status gwl_poisson(gwl_ctx* ctx, const void* rho, void* v, int n_fields, int
     GWL_CHECK(rho && v, GWL_EINVAL, "null pointer");
     check_precision(precision);
     const int chunk = std::max(2, std::min(n_fields + (n_fields & 1), 64));
-    ctx->ensure_work(chunk, 1, false);
+    ctx->ensure_fft(chunk);
     for (int f0 = 0; f0 < n_fields; f0 += chunk) {
       const int nf = std::min(chunk, n_fields - f0);
       if (precision == GWL_FP64)
@@ -1014,9 +1064,7 @@ gwl_status gwl_sigma_from_coeffs(gwl_ctx* ctx, const int* n_idx, int n_pairs, co
     GWL_HIP(hipMemcpy(ctx->norm2.p, p_norm2, sizeof(double) * n_pairs, hipMemcpyHostToDevice));
     GWL_HIP(hipMemcpy(ctx->out_len.p, lens, sizeof(int) * n_pairs, hipMemcpyHostToDevice));
     sigma_device(ctx, n_pairs, n_idx, ld, omega_ev, n_omega, eta_ev);
-    GWL_HIP(hipMemcpyAsync(sigma_out, ctx->sig.p, sizeof(double) * n_pairs * n_omega * 2,
-                           hipMemcpyDeviceToHost, ctx->stream));
-    GWL_HIP(hipStreamSynchronize(ctx->stream));
+    copy_out(ctx, sigma_out, ctx->sig.p, sizeof(double) * n_pairs * n_omega * 2);
   });
 }
 

@@ -574,23 +574,20 @@ void sum_rows(const double* part, long n, int rows, double scale, double* out, h
   GWL_HIP(hipGetLastError());
 }
 
-__global__ void row_norm2_kernel(const double* __restrict__ x, long n, double* __restrict__ out) {
-  __shared__ double red[NT];
+__global__ void __launch_bounds__(NTS)
+row_norm2_kernel(const double* __restrict__ x, long n, double* __restrict__ out) {
+  __shared__ double sh[NTS / 64];
   const double* xr = x + (long)blockIdx.x * n;
   double acc = 0.0;
-  for (long i = threadIdx.x; i < n; i += blockDim.x) acc += xr[i] * xr[i];
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int w = NT / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[blockIdx.x] = sqrt(red[0]);
+#pragma unroll 4
+  for (long i = threadIdx.x; i < n; i += NTS) acc += xr[i] * xr[i];
+  acc = block_sum(acc, sh);
+  if (threadIdx.x == 0) out[blockIdx.x] = sqrt(acc);
 }
 
 void row_norm2(const double* x, long n, int nrows, double* out, hipStream_t st) {
   if (nrows <= 0) return;
-  row_norm2_kernel<<<nrows, NT, 0, st>>>(x, n, out);
+  row_norm2_kernel<<<nrows, NTS, 0, st>>>(x, n, out);
   GWL_HIP(hipGetLastError());
 }
 

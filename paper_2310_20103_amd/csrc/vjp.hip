@@ -51,6 +51,30 @@ struct VjpSaved {
   DevBuf<int> ck_state, out_len, flen;
 };
 
+// Buffers of one call.  Kept in the context for the next call when they are
+// small: allocating, clearing and freeing some forty buffers takes 5.8 ms, as
+// much as the call's kernels on a small grid; large ones are given back.
+constexpr size_t kVjpKeep = 256u << 20;
+struct VjpWork {
+  DevBuf<double> store, Sv, KS, VS, US, UT, wbar, qb0, qb1, qb2, pend, dbar, dbar_tot, kbar, abar,
+      bbar, nbar, ebar, sig, Gd, e_d, eta_d, om_d, grad_int, gvpart;
+  DevBuf<int> qidx_d, slot_pair, mrow_d, nrow_d;
+  DevBuf<unsigned char> tscr;
+  std::shared_ptr<VjpSaved> full;  // checkpoints of a one-call VJP
+  size_t bytes() const {
+    size_t n = tscr.n + 4 * (qidx_d.n + slot_pair.n + mrow_d.n + nrow_d.n);
+    for (const DevBuf<double>* b :
+         {&store, &Sv, &KS, &VS, &US, &UT, &wbar, &qb0, &qb1, &qb2, &pend, &dbar, &dbar_tot, &kbar,
+          &abar, &bbar, &nbar, &ebar, &sig, &Gd, &e_d, &eta_d, &om_d, &grad_int, &gvpart})
+      n += 8 * b->n;
+    if (full)
+      for (const DevBuf<double>* b : {&full->ckq, &full->ckqp, &full->ck_amax, &full->ck_bprev,
+                                      &full->Pb, &full->Vnm})
+        n += 8 * b->n;
+    return n;
+  }
+};
+
 gwl_status vjp_run(gwl_ctx* ctx, VjpMode mode, const int* qp_states, int n_qp, int n_begin,
                    int n_end, const double* omega_ev, int n_omega, double eta_ev, int n_lanczos,
                    const double* grad_sigma, double* sigma_out, double* grad_energies,
@@ -149,13 +173,17 @@ gwl_status vjp_run(gwl_ctx* ctx, VjpMode mode, const int* qp_states, int n_qp, i
     // ---- segment store: per step t_0..t_g, K~t_0..K~t_{g-1}, w_k, V[t_0..t_{g-1}]
     const size_t per_step = (size_t)(2 * g + 2) * vec + (size_t)g * fld;
     int seg = std::max(1, (int)std::ceil(std::sqrt((double)L)));
-    DevBuf<double> store;
-    bool whole = false;
+    // (an exception drops the buffers with wk)
+    std::shared_ptr<VjpWork> wk = std::static_pointer_cast<VjpWork>(c.vjp_work);
+    c.vjp_work.reset();
+    if (!wk) wk = std::make_shared<VjpWork>();
+    DevBuf<double>& store = wk->store;
+    bool whole = false, sized = false;
     if (!persist && c.adjoint_store && seg < L &&
         ((size_t)L * per_step + 2 * vec) * sizeof(double) <= GWL_ADJOINT_STORE_MAX) {
       try {
-        store.ensure((size_t)L * per_step + 2 * vec);
-        whole = true;
+        store.ensure_zero((size_t)L * per_step + 2 * vec, st);
+        whole = sized = true;
         seg = L;
       } catch (const Error& e) {
         // not enough free device memory: recompute from checkpoints instead
@@ -164,7 +192,7 @@ gwl_status vjp_run(gwl_ctx* ctx, VjpMode mode, const int* qp_states, int n_qp, i
       }
     }
     if (seg >= L) whole = !persist, seg = L;
-    if (!store.p && !fwd_only) store.ensure((size_t)seg * per_step + 2 * vec);
+    if (!sized && !fwd_only) store.ensure_zero((size_t)seg * per_step + 2 * vec, st);
     c.adjoint_stored = whole ? 1 : 0;
     const int nseg = (L + seg - 1) / seg;
     // Full: the forward of a block ends by keeping its last segment's
@@ -172,17 +200,17 @@ gwl_status vjp_run(gwl_ctx* ctx, VjpMode mode, const int* qp_states, int n_qp, i
     const int nck = persist ? nseg : nseg - 1;  // checkpoints per block
     // q after the segment's last step, q_{k0-1} of the segment (no store in a
     // forward-only call)
-    double* const sq_end = store.p ? store.p + (size_t)seg * per_step : nullptr;
-    double* const sq_prev0 = store.p ? sq_end + vec : nullptr;
+    double* const sq_end = fwd_only ? nullptr : store.p + (size_t)seg * per_step;
+    double* const sq_prev0 = fwd_only ? nullptr : sq_end + vec;
     auto step_ptr = [&](int kk) { return store.p + (size_t)kk * per_step; };
 
     // buffers
     // kept state: in a new VjpSaved (Forward), the saved one (Backward), or a
     // local one for one block at a time (Full)
-    std::shared_ptr<VjpSaved> own;
     if (!bwd_only) {
-      own = std::make_shared<VjpSaved>();
-      sv = own;
+      if (persist || !wk->full) sv = std::make_shared<VjpSaved>();
+      else sv = wk->full;
+      if (!persist) wk->full = sv;
       const int nb_keep = persist ? nblk : 1;
       sv->Pb.ensure((size_t)nb_keep * vec);
       sv->Vnm.ensure((size_t)nb_keep * fld);
@@ -203,32 +231,37 @@ gwl_status vjp_run(gwl_ctx* ctx, VjpMode mode, const int* qp_states, int n_qp, i
     }
     // block bi's slot in the kept state
     auto kb = [&](int bi) { return persist ? (size_t)bi : (size_t)0; };
-    DevBuf<double> Sv, KS, VS, US, UT, wbar, qb0, qb1, qb2, pend, dbar, dbar_tot, kbar, abar,
-        bbar, nbar, ebar, sig, Gd, e_d, eta_d, om_d, grad_int, gvpart;
-    DevBuf<int> qidx_d, slot_pair, mrow_d, nrow_d;
-    DevBuf<unsigned char> tscr;
+    DevBuf<double>&Sv = wk->Sv, &KS = wk->KS, &VS = wk->VS, &US = wk->US, &UT = wk->UT,
+        &wbar = wk->wbar, &qb0 = wk->qb0, &qb1 = wk->qb1, &qb2 = wk->qb2, &pend = wk->pend,
+        &dbar = wk->dbar, &dbar_tot = wk->dbar_tot, &kbar = wk->kbar, &abar = wk->abar,
+        &bbar = wk->bbar, &nbar = wk->nbar, &ebar = wk->ebar, &sig = wk->sig, &Gd = wk->Gd,
+        &e_d = wk->e_d, &eta_d = wk->eta_d, &om_d = wk->om_d, &grad_int = wk->grad_int,
+        &gvpart = wk->gvpart;
+    DevBuf<int>&qidx_d = wk->qidx_d, &slot_pair = wk->slot_pair, &mrow_d = wk->mrow_d,
+        &nrow_d = wk->nrow_d;
+    DevBuf<unsigned char>& tscr = wk->tscr;
     if (!fwd_only) {
-      Sv.ensure((size_t)(g + 1) * vec);
-      KS.ensure((size_t)(g + 1) * vec);
-      VS.ensure((size_t)g * fld);
-      US.ensure((size_t)g * uvp);
-      UT.ensure((size_t)g * uvp);
-      wbar.ensure(vec);
-      qb0.ensure(vec);
-      qb1.ensure(vec);
-      qb2.ensure(vec);
-      pend.ensure(B);
-      dbar.ensure(vec);
-      dbar_tot.ensure(nvc);
-      kbar.ensure(vec);
-      grad_int.ensure((size_t)(d.nvp + d.ncp) * d.nrp);
-      gvpart.ensure((size_t)nct * c.nv * d.nrp);
+      Sv.ensure_zero((size_t)(g + 1) * vec, st);
+      KS.ensure_zero((size_t)(g + 1) * vec, st);
+      VS.ensure_zero((size_t)g * fld, st);
+      US.ensure_zero((size_t)g * uvp, st);
+      UT.ensure_zero((size_t)g * uvp, st);
+      wbar.ensure_zero(vec, st);
+      qb0.ensure_zero(vec, st);
+      qb1.ensure_zero(vec, st);
+      qb2.ensure_zero(vec, st);
+      pend.ensure_zero(B, st);
+      dbar.ensure_zero(vec, st);
+      dbar_tot.ensure_zero(nvc, st);
+      kbar.ensure_zero(vec, st);
+      grad_int.ensure_zero((size_t)(d.nvp + d.ncp) * d.nrp, st);
+      gvpart.ensure_zero((size_t)nct * c.nv * d.nrp, st);
     }
-    abar.ensure((size_t)P * L);
-    bbar.ensure((size_t)P * L);
-    nbar.ensure(P);
-    ebar.ensure(P);
-    sig.ensure((size_t)P * n_omega * 2);
+    abar.ensure_zero((size_t)P * L, st);
+    bbar.ensure_zero((size_t)P * L, st);
+    nbar.ensure_zero(P, st);
+    ebar.ensure_zero(P, st);
+    sig.ensure_zero((size_t)P * n_omega * 2, st);
     Gd.ensure((size_t)n_qp * n_omega * 2);
     e_d.ensure(P);
     eta_d.ensure(P);
@@ -237,7 +270,7 @@ gwl_status vjp_run(gwl_ctx* ctx, VjpMode mode, const int* qp_states, int n_qp, i
     slot_pair.ensure(B);
     mrow_d.ensure(P);
     nrow_d.ensure(P);
-    tscr.ensure((size_t)B * L * n_omega * 16);
+    tscr.ensure_zero((size_t)B * L * n_omega * 16, st);
     std::vector<int> mr(P), nr_(P);
     for (int p = 0; p < P; ++p) {
       mr[p] = c.orb_row(m[p]);
@@ -492,6 +525,7 @@ gwl_status vjp_run(gwl_ctx* ctx, VjpMode mode, const int* qp_states, int n_qp, i
       sv->nvc = nvc;
       sv->nrp = d.nrp;
       c.vjp_saved = sv;
+      if (wk->bytes() <= kVjpKeep) c.vjp_work = wk;
       set_error("");
       return GWL_OK;
     }
@@ -523,6 +557,7 @@ gwl_status vjp_run(gwl_ctx* ctx, VjpMode mode, const int* qp_states, int n_qp, i
                              hipMemcpyDeviceToHost, st));
     }
     GWL_HIP(hipStreamSynchronize(st));
+    if (wk->bytes() <= kVjpKeep) c.vjp_work = wk;
     set_error("");
     return GWL_OK;
   } catch (const Error& e) {
