@@ -10,6 +10,7 @@
 #include <cstring>
 #include <memory>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "common.h"
@@ -142,6 +143,7 @@ struct gwl_ctx {
   int fp64_kernel = 1;  // 0 = plain FMA tiles, 1 = MFMA (both precisions)
   int bf16_tile = 256;  // block tile width of the second 16-bit MFMA GEMM
   bool tile_fixed = false;  // set by the caller: the autotuner keeps it
+  bool tuning = false;      // autotuner at work: bf16_tile is the candidate
   int tda = 0;          // 1: Tamm-Dancoff (Lanczos on A = Delta + K from (nm|vc))
   int quadrature = 0;   // 1: Lanczos on C + Gauss quadrature (no polynomial)
   int adjoint_store = 0;     // 1: the adjoint keeps the forward's iterates when they fit
@@ -253,7 +255,7 @@ struct gwl_ctx {
   std::vector<unsigned char> sg_key;
   DevBuf<int> sched_tab;            // refill schedule of the current run_pairs call
   hipGraphExec_t dgraph = nullptr;
-  int dg_nb = -1, dg_prec = -1, dg_S = -1, dg_kern = -1, dg_deg = -1;
+  int dg_nb = -1, dg_prec = -1, dg_S = -1, dg_kern = -1, dg_deg = -1, dg_tile = -1;
   double dg_lo = 0, dg_hi = 0, dg_uscale = 0;
   long work_gen = 0, dg_gen = -1;
 
@@ -386,15 +388,47 @@ struct gwl_ctx {
       }
       return best;
     }
-    long blocks;
-    if (!fp64_kernel)
-      blocks = (long)nb * (d.nvp / 64) * ceil_div(d.ncp, 64);
-    else
-      blocks = gemm2_f16_blocks(d, nb, bf16_tile);
+    if (fp64_kernel && !tuning) return model16(nb, d, tile16(nb)).second;
+    return fill_splitk(nb, d);
+  }
+  // Split that fills the chip (about 1024 blocks) while each split keeps >= 512
+  // grid points: the plain FMA tiles', where the autotuner starts, and the least
+  // that the mixed GEMM's model may take (its FP32 sums get no longer).
+  int fill_splitk(int nb, const GemmDims& d) const {
+    const long blocks = fp64_kernel ? gemm2_f16_blocks(d, nb, bf16_tile)
+                                    : (long)nb * (d.nvp / 64) * ceil_div(d.ncp, 64);
     int s = 1;
-    // fill the chip (about 1024 blocks) while each split keeps >= 512 grid points
     while (blocks * s < 1024 && s < 32 && (long)d.nrp / (s * 2) >= 512) s *= 2;
     return s;
+  }
+  // Time (us) and split of the mixed second GEMM with block tiles `tile` wide.  A
+  // K step of 32 measured, from the slope of whole products over the split: 256
+  // wide 0.73 to 0.87 us alone, 0.92 with the chip full; 128 wide 0.62 to 0.73
+  // alone, 0.57 beside a second block of the CU.  Six more steps per block (an
+  // estimate of fill and epilogue), and partial tiles written and read once.
+  // With few vectors 32 splits leave most CUs idle.  Whole products, before
+  // (tile 256, 32 splits) and with this rule: 48^3, 50 + 200 orbitals, 5 vectors
+  // 199 and 147 us; 64^3, 100 + 300, 1 vector 348 and 247; 64 x 64 x 54, 44 + 158,
+  // 20 vectors 433 and 381.
+  std::pair<double, int> model16(int nb, const GemmDims& d, int tile) const {
+    const long tiles = gemm2_f16_blocks(d, nb, tile);
+    const int smax = (int)std::max<long>(1, std::min<long>(max_splitk(nb), d.nrp / 256));
+    const int smin = std::min(smax, fill_splitk(nb, d));
+    std::pair<double, int> best{1e300, 1};
+    for (int s = smin; s <= smax; ++s) {
+      const long per_cu = ceil_div(tiles * s, 256);
+      const double step = tile == 256 ? 0.92 * per_cu : per_cu == 1 ? 0.65 : 0.57 * per_cu;
+      const double us = step * (ceil_div(d.nrp, 32L * s) + 6) +
+                        (double)s * nb * d.nvp * d.ncp * 8.0 / 4.8e6;
+      if (us < best.first) best = {us, s};
+    }
+    return best;
+  }
+  // Block tile of the mixed second GEMM for nb vectors: the caller's, the tuned
+  // one at the tuned batch, else the model's.
+  int tile16(int nb) const {
+    if (tile_fixed || tuned[GWL_MIXED_F16].B == nb || !fp64_kernel || tuning) return bf16_tile;
+    return model16(nb, kd(), 128).first < 0.97 * model16(nb, kd(), 256).first ? 128 : 256;
   }
   // Splits the partial sums' buffer has room for, whatever the batch it was
   // sized for: small batches may take more (they have few tiles).
@@ -546,7 +580,7 @@ struct gwl_ctx {
       const f16_t* pc = pt + orb16_index(d, d.nvp, 0);  // the conduction rows follow
       prof_begin();
       if (fp64_kernel)
-        gemm2_f16(d, nb, bf16_tile, S, pv, pc, vpot16.p, yp, st);
+        gemm2_f16(d, nb, tile16(nb), S, pv, pc, vpot16.p, yp, st);
       else
         gemm2_f16s(d, nb, S, pv, pc, vpot16.p, yp, st);
       prof_end(1, nb);
@@ -700,7 +734,7 @@ struct gwl_ctx {
     }
     if (!dgraph || dg_nb != nb || dg_prec != prec || dg_S != S || dg_kern != fp64_kernel ||
         dg_gen != work_gen || dg_deg != poly_degree || dg_lo != poly_lo || dg_hi != poly_hi ||
-        dg_uscale != u_scale) {
+        dg_uscale != u_scale || dg_tile != tile16(nb)) {
       drop_graph();
       hipGraph_t g = nullptr;
       GWL_HIP(hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal));
@@ -727,6 +761,7 @@ struct gwl_ctx {
       dg_lo = poly_lo;
       dg_hi = poly_hi;
       dg_uscale = u_scale;
+      dg_tile = tile16(nb);
     }
     GWL_HIP(hipGraphLaunch(dgraph, stream));
   }
@@ -802,6 +837,11 @@ struct gwl_ctx {
     GWL_HIP(hipEventCreate(&e0));
     GWL_HIP(hipEventCreate(&e1));
     best.us_per_vec = 1e300;
+    struct Tuning {
+      bool& on;
+      ~Tuning() { on = false; }
+    } tuning_guard{tuning};
+    tuning = true;
     try {
       for (int tile : tiles) {
         bf16_tile = tile;
@@ -961,7 +1001,7 @@ struct gwl_ctx {
     key.kern = fp64_kernel;
     key.deg = poly_degree;
     key.reorth = reorth;
-    key.tile = bf16_tile;
+    key.tile = tile16(B);
     key.gen = work_gen;
     key.lo = poly_lo;
     key.hi = poly_hi;

@@ -682,7 +682,7 @@ gwl_status gwl_potential_product(gwl_ctx* ctx, const double* v, double* y, int n
         const f16_t* pc = pt + orb16_index(d, d.nvp, 0);
         float* yp = reinterpret_cast<float*>(c.ypart.p);
         if (c.fp64_kernel)
-          gemm2_f16(d, nb, c.bf16_tile, S, pt, pc, c.vpot16.p, yp, st);
+          gemm2_f16(d, nb, c.tile16(nb), S, pt, pc, c.vpot16.p, yp, st);
         else
           gemm2_f16s(d, nb, S, pt, pc, c.vpot16.p, yp, st);
         const double os = c.orb16_scale;
