@@ -115,7 +115,7 @@ void copy_out(gwl_ctx* ctx, void* dst, const void* src, size_t bytes) {
   if (staged) {
     hipPointerAttribute_t at;
     if (hipPointerGetAttributes(&at, dst) == hipSuccess)
-      staged = at.type != hipMemoryTypeHost;
+      staged = at.type == hipMemoryTypeUnregistered;  // (memcpy writes it below)
     else
       (void)hipGetLastError();  // (ordinary memory, to some versions)
   }
