@@ -438,7 +438,7 @@ enum {
   GWL_KEY_PROF_MS_GEMM2 = 17,   /* query: same for the second GEMM */
   GWL_KEY_PROF_N_GEMM2 = 18,
   GWL_KEY_PROF_VEC_GEMM2 = 19,
-  GWL_KEY_PROF_MS_FFT = 20,     /* query: same for the Poisson solve (all five passes) */
+  GWL_KEY_PROF_MS_FFT = 20,     /* query: same for the Poisson solve (all its passes) */
   GWL_KEY_PROF_N_FFT = 21,
   GWL_KEY_PROF_VEC_FFT = 22,
   GWL_KEY_GRAPHS = 23,          /* set/query: 1 (default) = replay a captured HIP graph of the
@@ -512,9 +512,9 @@ enum {
 #define GWL_ADJOINT_STORE_MAX (32ull << 30)
 /* The autotuner runs on the first gwl_sigma_c / gwl_sigma_c_range /
  * gwl_lanczos_pairs call with block = 0: it times one C-product for
- * B in {32, 64, 128, 256} and three splits of the second GEMM, and for the
- * mixed product both block tiles of the second GEMM (unless
- * GWL_KEY_BF16_TILE fixed one).  If the environment variable GWL_TUNE_CACHE
+ * B in {32, 64, 128, 256}, and for the mixed product also three splits and
+ * both block tiles of the second GEMM (unless GWL_KEY_BF16_TILE fixed one);
+ * the FP64 MFMA kernels' split follows from the sizes.  If the environment variable GWL_TUNE_CACHE
  * names a file, choices are read from and appended to it (text lines
  * "gfx950:N_r:N_v:N_c:precision:kernels:fixed_tile:n_mu B split tile us"). */
 

@@ -719,7 +719,7 @@ struct gwl_ctx {
   }
 
   // w = p_g(C) q over nb slots; replays a captured graph of the whole product
-  // (g x [first GEMM, five FFT passes, second GEMM, combine] + cast) when the
+  // (g x [first GEMM, FFT passes, second GEMM, combine] + cast) when the
   // shapes and buffers are unchanged.
   void apply_d_step(int nb, int prec) {
     last_c_matvecs += (long)nb * poly_degree;

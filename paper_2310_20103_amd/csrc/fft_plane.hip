@@ -20,14 +20,14 @@
 // addresses along z in the y and x steps, runs of R2 (read) or R1 (written)
 // points in the z steps.
 //
-// Bound by HBM from a few hundred planes on (64 fields of 64^3 in FP64: 182 us
+// Bound by HBM from a few hundred planes on (64 fields of 64^3 in FP64: 177 us
 // per call for 1.07 GB over the three passes), by latency below; small planes
 // run in blocks of one to a few waves, so many share a CU.  Against stage-by-
 // stage transforms with ping-pong buffers and line lengths known at run time: 32
-// fields of 128^3 in FP32 (then five passes) 1,056 -> 491 us per call, 128 of
-// 48^3 in FP32 325 -> 114, 64 of 32^3 in FP64 95 -> 54, two of 24^3 in FP64
+// fields of 128^3 in FP32 (then five passes) 1,055 -> 488 us per call, 128 of
+// 48^3 in FP32 320 -> 107, 64 of 32^3 in FP64 92 -> 52, two of 24^3 in FP64
 // 34.5 -> 28.2; against in-place radix-8 stages of 64^3 with load and store
-// phases of their own, 128 fields in FP32 227 -> 192.  Cutting the batch into runs
+// phases of their own, 128 fields in FP32 211 -> 186.  Cutting the batch into runs
 // whose spectrum stays in the 256 MB cache gained nothing at 140 MB and lost
 // 9 % at 70 MB.
 #include <algorithm>
