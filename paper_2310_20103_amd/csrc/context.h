@@ -41,6 +41,7 @@ struct DevBuf {
     hipError_t e = hipMalloc((void**)&p, cnt * sizeof(T));
     if (e != hipSuccess) {
       p = nullptr;
+      (void)hipGetLastError();  // (reported here, not by the next launch)
       throw Error{GWL_ENOMEM, "hipMalloc of " + std::to_string(cnt * sizeof(T)) +
                                   " bytes failed: " + hipGetErrorString(e)};
     }
@@ -439,6 +440,12 @@ struct gwl_ctx {
     const long nvpc = (long)gd.nvp * gd.ncp;
     if (nb > cap) {
       ++work_gen;
+      // A buffer is given up before the larger one is there: no capacity until
+      // all of them are, and no fill left running when one fails.
+      cap = 0;
+      struct Fills {
+        ~Fills() { (void)hipDeviceSynchronize(); }
+      } fills;
       q.ensure((size_t)nb * nvc, false);
       qprev.ensure((size_t)nb * nvc, false);
       w.ensure((size_t)nb * nvc, false);
@@ -481,8 +488,12 @@ struct gwl_ctx {
   // the Poisson scratch alone, for nf fields
   void ensure_fft(int nf) {
     const size_t need = (size_t)((nf + 1) / 2) * nr * 16;
-    if (need > fftx.n) ++work_gen;  // (captured graphs hold its address)
+    if (need <= fftx.n) return;
+    ++work_gen;  // (captured graphs hold its address)
+    const int had = cap;
+    cap = 0;  // (the products' scratch too: should it fail, ensure_work allocates again)
     fftx.ensure(need);
+    cap = had;
   }
 
   int orb_row(int n) const { return n < nv ? n : gd.nvp + (n - nv); }

@@ -1,0 +1,107 @@
+"""Host side of the library on the CPU: libgwl.so is loaded over a stand-in for
+the HIP runtime (fake_hip.cpp: device memory in host memory, kernel launches
+logged and not run), in a process of its own for each test.  What is checked is
+allocation, its failures and the launches; results mean nothing here."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+LIB = os.path.join(ROOT, "paper_2310_20103_amd", "_lib", "libgwl.so")
+
+pytestmark = pytest.mark.skipif(not os.path.exists(LIB), reason="libgwl.so not built")
+
+PREAMBLE = '''
+import ctypes as ct, importlib.util, sys
+import numpy as np
+fake = ct.CDLL(sys.argv[1], mode=ct.RTLD_GLOBAL)
+fake.fake_log.restype = ct.c_char_p
+fake.fake_watched.restype = ct.c_double
+for f, t in (("fake_live", ct.c_size_t), ("fake_mallocs", ct.c_long)):
+    getattr(fake, f).restype = t
+for f in ("fake_fail_malloc", "fake_fail_event", "fake_limit"):
+    getattr(fake, f).argtypes = [ct.c_size_t if f == "fake_limit" else ct.c_long]
+fake.fake_watch.argtypes = [ct.c_char_p, ct.c_int, ct.c_long]
+sys.modules["torch"] = None  # (its own HIP runtime stays out of this process)
+spec = importlib.util.spec_from_file_location("binding", sys.argv[2])
+G = importlib.util.module_from_spec(spec)
+spec.loader.exec_module(G)
+L = G.lib()
+
+def context(nv, nc, grid, **kw):
+    rng = np.random.default_rng(1)
+    kw.setdefault("poly_lo", 0.01)
+    kw.setdefault("poly_hi", 1.0)
+    e = np.concatenate([np.linspace(-9, -5, nv), np.linspace(1, 9, nc)])
+    c = G.Context(rng.standard_normal((nv + nc, int(np.prod(grid)))), e, nv, grid, 6.0, **kw)
+    fake.fake_reset()
+    return c
+
+def log():
+    return fake.fake_log().decode().splitlines()
+
+def call(name, c, n_vec, *a):
+    """A component call on host arrays (the stand-in's device memory)."""
+    width = {"gwl_apply_c": (c.n_vc, c.n_vc), "gwl_poisson": (c.n_r, c.n_r),
+             "gwl_pair_density": (c.n_vc, c.n_r), "gwl_potential_product": (c.n_r, c.n_vc)}[name]
+    x, y = np.zeros((n_vec, width[0])), np.zeros((n_vec, width[1]))
+    return getattr(L, name)(c._h, G._ptr(x), G._ptr(y), n_vec, *(a or (0,)))
+'''
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("fake") / "libfakehip.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-o", so,
+                    os.path.join(HERE, "fake_hip.cpp")], check=True)
+    return so
+
+
+def run(fake, body):
+    r = subprocess.run([sys.executable, "-c", PREAMBLE + body, fake,
+                        os.path.join(ROOT, "paper_2310_20103_amd", "binding.py")],
+                       capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-4000:]
+
+
+@pytest.mark.parametrize("k", range(0, 30, 3))
+def test_growth_that_fails(fake, k):
+    """The k-th allocation of a growth fails: the call says so, and a smaller
+    one afterwards works on whole, cleared buffers."""
+    run(fake, f'''
+c = context(3, 5, (4, 6, 4))
+assert call("gwl_apply_c", c, 4) == 0
+fake.fake_reset()
+fake.fake_fail_malloc({k})
+code = call("gwl_apply_c", c, 40)
+grown = fake.fake_mallocs()
+assert code == (G.GWL_ENOMEM if {k} < grown else 0), code
+fake.fake_reset()
+# the buffers given up are allocated again before a kernel runs on them
+assert call("gwl_poisson", c, 8) == 0
+assert call("gwl_apply_c", c, 4) == 0
+if code:
+    assert fake.fake_mallocs() >= 1
+    lines = log()
+    assert lines and not any(l.endswith("unsynced") for l in lines), lines
+    fake.fake_reset()
+    assert call("gwl_apply_c", c, 40) == 0
+    assert call("gwl_apply_c", c, 40) == 0
+''')
+
+
+def test_scratch_growth_that_fails(fake):
+    """The Poisson scratch alone fails to grow: products afterwards have theirs."""
+    run(fake, '''
+c = context(3, 5, (4, 6, 4))
+assert call("gwl_apply_c", c, 4) == 0
+fake.fake_reset()
+fake.fake_fail_malloc(0)
+assert call("gwl_poisson", c, 60) == G.GWL_ENOMEM
+fake.fake_reset()
+assert call("gwl_apply_c", c, 4) == 0
+assert fake.fake_mallocs() == 1  # the scratch
+''')
