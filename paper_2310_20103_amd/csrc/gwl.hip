@@ -120,12 +120,19 @@ void copy_out(gwl_ctx* ctx, void* dst, const void* src, size_t bytes) {
       (void)hipGetLastError();  // (ordinary memory, to some versions)
   }
   if (staged && !ctx->pin) {
-    if (hipHostMalloc((void**)&ctx->pin, 2 * chunk, hipHostMallocDefault) == hipSuccess) {
-      for (auto& e : ctx->pin_ev)
-        if (!e) GWL_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    } else {
+    unsigned char* p = nullptr;
+    hipEvent_t ev[2] = {nullptr, nullptr};
+    if (hipHostMalloc((void**)&p, 2 * chunk, hipHostMallocDefault) == hipSuccess &&
+        hipEventCreateWithFlags(&ev[0], hipEventDisableTiming) == hipSuccess &&
+        hipEventCreateWithFlags(&ev[1], hipEventDisableTiming) == hipSuccess) {
+      ctx->pin = p;
+      ctx->pin_ev[0] = ev[0];
+      ctx->pin_ev[1] = ev[1];
+    } else {  // the plain copy, this time
       (void)hipGetLastError();
-      ctx->pin = nullptr;
+      for (auto e : ev)
+        if (e) (void)hipEventDestroy(e);
+      if (p) (void)hipHostFree(p);
       staged = false;
     }
   }

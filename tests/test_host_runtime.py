@@ -105,3 +105,30 @@ fake.fake_reset()
 assert call("gwl_apply_c", c, 4) == 0
 assert fake.fake_mallocs() == 1  # the scratch
 ''')
+
+
+@pytest.mark.parametrize("k", [0, 1])
+@pytest.mark.parametrize("what", ["malloc", "event"])
+def test_staging_that_cannot_be_made(fake, what, k):
+    """A large result without its pinned chunks or an event: copied plainly, now
+    and in the calls that follow, and nothing is left allocated."""
+    run(fake, f'''
+c = context(3, 5, (4, 6, 4))
+args = ([0, 4], np.ones((2, 3)), np.ones((2, 3)), np.ones(2), [3, 3], np.linspace(-1, 1, 200000), 0.1)
+c.sigma_from_coeffs([0, 4], *args[1:5], args[5][:9], 0.1)
+big = 2 * 200000 * 16
+live = fake.fake_live()
+fake.fake_reset()
+if "{what}" == "event":
+    fake.fake_fail_event({k})
+else:
+    fake.fake_limit(live + big + 200000 * 8 + 10000 + {k} * (2 << 20))
+for _ in range(2):
+    c.sigma_from_coeffs(*args)
+    assert fake.fake_live() < live + big + 200000 * 8 + 100000
+    if "{what}" == "event":
+        fake.fake_fail_event(0)
+fake.fake_reset()
+c.sigma_from_coeffs(*args)
+assert fake.fake_live() >= live + big + (4 << 20)
+''')
