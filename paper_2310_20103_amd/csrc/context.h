@@ -19,6 +19,10 @@
 namespace gwl {
 
 
+// What a failed allocation of this thread may give back: set while a call runs
+// on a context that keeps buffers it does not need (ContextCall).
+inline thread_local std::shared_ptr<void>* spare_memory = nullptr;
+
 template <typename T>
 struct DevBuf {
   T* p = nullptr;
@@ -39,6 +43,11 @@ struct DevBuf {
     release();
     if (cnt == 0) return;
     hipError_t e = hipMalloc((void**)&p, cnt * sizeof(T));
+    if (e != hipSuccess && spare_memory && *spare_memory) {
+      (void)hipGetLastError();
+      spare_memory->reset();
+      e = hipMalloc((void**)&p, cnt * sizeof(T));
+    }
     if (e != hipSuccess) {
       p = nullptr;
       (void)hipGetLastError();  // (reported here, not by the next launch)
@@ -1440,4 +1449,16 @@ struct gwl_ctx {
                   ", " + std::to_string(poly_hi) + "] hartree^2 (" + std::to_string(nbad) +
                   " of " + std::to_string(P) + " runs): p_g(C) is no square root there");
   }
+};
+
+// One call on a context: the buffers kept from an earlier gradient go before an
+// allocation of the call fails.
+struct ContextCall {
+  explicit ContextCall(gwl_ctx* ctx) {
+    GWL_CHECK(ctx != nullptr, GWL_EINVAL, "null context");
+    spare_memory = &ctx->vjp_work;
+  }
+  ~ContextCall() { spare_memory = nullptr; }
+  ContextCall(const ContextCall&) = delete;
+  ContextCall& operator=(const ContextCall&) = delete;
 };

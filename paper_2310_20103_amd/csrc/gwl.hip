@@ -71,8 +71,6 @@ void upload_tables(int n, double len, DevBuf<cplx<T>>& tw, DevBuf<T>& g2) {
   GWL_HIP(hipMemcpy(g2.p, gg.data(), n * sizeof(T), hipMemcpyHostToDevice));
 }
 
-void check_ctx(gwl_ctx* c) { GWL_CHECK(c != nullptr, GWL_EINVAL, "null context"); }
-
 // The two built precisions; the split-BF16 and FP32 members of gwl_precision
 // are named by the ABI but not built.
 void check_precision(int p) {
@@ -454,7 +452,7 @@ void gwl_destroy(gwl_ctx* ctx) {
 
 gwl_status gwl_set_option(gwl_ctx* ctx, int key, double value) {
   return guarded([&] {
-    check_ctx(ctx);
+    const ContextCall call(ctx);
     switch (key) {
       case GWL_KEY_PRECISION:
         check_precision((int)value);
@@ -523,7 +521,7 @@ gwl_status gwl_set_option(gwl_ctx* ctx, int key, double value) {
 
 gwl_status gwl_query(gwl_ctx* ctx, int key, double* out) {
   return guarded([&] {
-    check_ctx(ctx);
+    const ContextCall call(ctx);
     GWL_CHECK(out != nullptr, GWL_EINVAL, "null output");
     switch (key) {
       case GWL_KEY_PRECISION: *out = ctx->precision; break;
@@ -567,7 +565,7 @@ gwl_status gwl_query(gwl_ctx* ctx, int key, double* out) {
 
 gwl_status gwl_poisson(gwl_ctx* ctx, const void* rho, void* v, int n_fields, int precision) {
   return guarded([&] {
-    check_ctx(ctx);
+    const ContextCall call(ctx);
     GWL_CHECK(n_fields >= 0, GWL_EINVAL, "n_fields < 0");
     if (n_fields == 0) return;
     GWL_CHECK(rho && v, GWL_EINVAL, "null pointer");
@@ -593,7 +591,7 @@ gwl_status gwl_poisson(gwl_ctx* ctx, const void* rho, void* v, int n_fields, int
 
 gwl_status gwl_apply_c(gwl_ctx* ctx, const double* x, double* y, int n_vec, int precision) {
   return guarded([&] {
-    check_ctx(ctx);
+    const ContextCall call(ctx);
     GWL_CHECK(n_vec >= 0, GWL_EINVAL, "n_vec < 0");
     if (n_vec == 0) return;
     GWL_CHECK(x && y, GWL_EINVAL, "null pointer");
@@ -614,7 +612,7 @@ gwl_status gwl_apply_c(gwl_ctx* ctx, const double* x, double* y, int n_vec, int 
 gwl_status gwl_pair_density(gwl_ctx* ctx, const double* x, double* rho, int n_vec,
                             int precision) {
   return guarded([&] {
-    check_ctx(ctx);
+    const ContextCall call(ctx);
     GWL_CHECK(n_vec >= 0, GWL_EINVAL, "n_vec < 0");
     if (n_vec == 0) return;
     GWL_CHECK(x && rho, GWL_EINVAL, "null pointer");
@@ -652,7 +650,7 @@ gwl_status gwl_pair_density(gwl_ctx* ctx, const double* x, double* rho, int n_ve
 gwl_status gwl_potential_product(gwl_ctx* ctx, const double* v, double* y, int n_vec,
                                  int precision) {
   return guarded([&] {
-    check_ctx(ctx);
+    const ContextCall call(ctx);
     GWL_CHECK(n_vec >= 0, GWL_EINVAL, "n_vec < 0");
     if (n_vec == 0) return;
     GWL_CHECK(v && y, GWL_EINVAL, "null pointer");
@@ -706,7 +704,7 @@ gwl_status gwl_potential_product(gwl_ctx* ctx, const double* v, double* y, int n
 
 gwl_status gwl_apply_d(gwl_ctx* ctx, const double* x, double* y, int n_vec, int precision) {
   return guarded([&] {
-    check_ctx(ctx);
+    const ContextCall call(ctx);
     GWL_CHECK(n_vec >= 0, GWL_EINVAL, "n_vec < 0");
     if (n_vec == 0) return;
     GWL_CHECK(x && y, GWL_EINVAL, "null pointer");
@@ -728,7 +726,7 @@ gwl_status gwl_apply_d(gwl_ctx* ctx, const double* x, double* y, int n_vec, int 
 
 gwl_status gwl_sigma_x(gwl_ctx* ctx, const int* qp_states, int n_qp, double* sigma_x_out) {
   return guarded([&] {
-    check_ctx(ctx);
+    const ContextCall call(ctx);
     GWL_CHECK(n_qp >= 0, GWL_EINVAL, "n_qp < 0");
     if (n_qp == 0) return;
     GWL_CHECK(qp_states && sigma_x_out, GWL_EINVAL, "null pointer");
@@ -830,7 +828,7 @@ gwl_status gwl_qp_solve(const double* omega_ev, int n_omega, const double* sigma
 
 gwl_status gwl_coupling(gwl_ctx* ctx, const int* m_idx, const int* n_idx, int count, double* p) {
   return guarded([&] {
-    check_ctx(ctx);
+    const ContextCall call(ctx);
     GWL_CHECK(count >= 0, GWL_EINVAL, "count < 0");
     if (count == 0) return;
     GWL_CHECK(m_idx && n_idx && p, GWL_EINVAL, "null pointer");
@@ -851,7 +849,7 @@ gwl_status gwl_lanczos_pairs(gwl_ctx* ctx, const int* m_idx, const int* n_idx, c
                              int n_pairs, double* alpha, double* beta, double* p_norm2,
                              int* out_len_h, int ld) {
   return guarded([&] {
-    check_ctx(ctx);
+    const ContextCall call(ctx);
     GWL_CHECK(n_pairs >= 0, GWL_EINVAL, "n_pairs < 0");
     if (n_pairs == 0) return;
     GWL_CHECK(m_idx && n_idx && lengths && alpha && beta && p_norm2, GWL_EINVAL,
@@ -944,7 +942,7 @@ gwl_status gwl_sigma_c_range(gwl_ctx* ctx, const int* qp_states, int n_qp, int n
                              int n_end, const double* omega_ev, int n_omega, double eta_ev,
                              int n_lanczos, double* sigma_out) {
   return guarded([&] {
-    check_ctx(ctx);
+    const ContextCall call(ctx);
     GWL_CHECK(n_qp >= 0 && n_omega >= 0, GWL_EINVAL, "negative count");
     GWL_CHECK(n_begin >= 0 && n_begin < n_end && n_end <= ctx->n_orb, GWL_EINVAL,
               "need 0 <= n_begin < n_end <= n_orb");
@@ -997,7 +995,7 @@ gwl_status gwl_sigma_c(gwl_ctx* ctx, const int* qp_states, int n_qp, const doubl
 gwl_status gwl_sigma_c_offdiag(gwl_ctx* ctx, int m, int m2, const double* omega_ev, int n_omega,
                                double eta_ev, int n_lanczos, double* sigma_out) {
   return guarded([&] {
-    check_ctx(ctx);
+    const ContextCall call(ctx);
     GWL_CHECK(n_omega >= 0, GWL_EINVAL, "negative count");
     if (n_omega == 0) return;
     GWL_CHECK(omega_ev && sigma_out, GWL_EINVAL, "null pointer");
@@ -1051,7 +1049,7 @@ gwl_status gwl_sigma_from_coeffs(gwl_ctx* ctx, const int* n_idx, int n_pairs, co
                                  int ld, const double* omega_ev, int n_omega, double eta_ev,
                                  double* sigma_out) {
   return guarded([&] {
-    check_ctx(ctx);
+    const ContextCall call(ctx);
     GWL_CHECK(n_pairs >= 0 && n_omega >= 0, GWL_EINVAL, "negative count");
     if (n_pairs == 0 || n_omega == 0) return;
     GWL_CHECK(n_idx && alpha && beta && p_norm2 && lens && omega_ev && sigma_out, GWL_EINVAL,

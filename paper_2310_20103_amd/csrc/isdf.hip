@@ -118,7 +118,7 @@ void gwl_ctx::set_isdf(int on) {
 
 extern "C" gwl_status gwl_isdf_setup(gwl_ctx* ctx, const int* points, int n_mu) {
   try {
-    GWL_CHECK(ctx != nullptr, GWL_EINVAL, "null context");
+    const ContextCall call(ctx);
     gwl_ctx& c = *ctx;
     GWL_CHECK(points != nullptr, GWL_EINVAL, "null pointer");
     GWL_CHECK(n_mu >= 1 && n_mu <= c.nr, GWL_EINVAL, "need 1 <= n_mu <= N_r");

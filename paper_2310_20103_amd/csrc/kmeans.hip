@@ -198,7 +198,7 @@ extern "C" gwl_status gwl_isdf_kmeans(gwl_ctx* ctx, const int* init_points, int 
                                       int max_iter, int* points_out, int* n_points,
                                       int* n_assign) {
   try {
-    GWL_CHECK(ctx != nullptr, GWL_EINVAL, "null context");
+    const ContextCall call(ctx);
     gwl_ctx& c = *ctx;
     GWL_CHECK(init_points && points_out && n_points && n_assign, GWL_EINVAL, "null pointer");
     GWL_CHECK(n_init >= 1 && n_init <= c.nr, GWL_EINVAL, "need 1 <= n_init <= N_r");

@@ -176,7 +176,7 @@ using namespace gwl;
 extern "C" gwl_status gwl_isdf_qrcp(gwl_ctx* ctx, const double* gv, const double* gc, int p,
                                     int n_mu, int* points_out) {
   try {
-    GWL_CHECK(ctx != nullptr, GWL_EINVAL, "null context");
+    const ContextCall call(ctx);
     gwl_ctx& c = *ctx;
     GWL_CHECK(gv && gc && points_out, GWL_EINVAL, "null pointer");
     GWL_CHECK(p >= 1 && n_mu >= 1 && n_mu <= p && (long)n_mu <= c.nr, GWL_EINVAL,

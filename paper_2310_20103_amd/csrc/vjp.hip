@@ -75,12 +75,12 @@ struct VjpWork {
   }
 };
 
-gwl_status vjp_run(gwl_ctx* ctx, VjpMode mode, const int* qp_states, int n_qp, int n_begin,
+gwl_status vjp_once(gwl_ctx* ctx, VjpMode mode, const int* qp_states, int n_qp, int n_begin,
                    int n_end, const double* omega_ev, int n_omega, double eta_ev, int n_lanczos,
                    const double* grad_sigma, double* sigma_out, double* grad_energies,
                    void* grad_orbitals) {
   try {
-    GWL_CHECK(ctx != nullptr, GWL_EINVAL, "null context");
+    const ContextCall call(ctx);
     gwl_ctx& c = *ctx;
     const bool fwd_only = mode == VjpMode::Forward, bwd_only = mode == VjpMode::Backward;
     const bool persist = mode != VjpMode::Full;  // checkpoints of every block kept
@@ -567,6 +567,15 @@ gwl_status vjp_run(gwl_ctx* ctx, VjpMode mode, const int* qp_states, int n_qp, i
     set_error(e.what());
     return GWL_EDEVICE;
   }
+}
+
+// Once more without the buffers kept from the call before, should they be what
+// is in the way (a failed call drops them).
+template <typename... A>
+gwl_status vjp_run(gwl_ctx* ctx, A... a) {
+  const bool kept = ctx && ctx->vjp_work;
+  const gwl_status s = vjp_once(ctx, a...);
+  return kept && s == GWL_ENOMEM ? vjp_once(ctx, a...) : s;
 }
 
 }  // namespace

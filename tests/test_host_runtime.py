@@ -132,3 +132,35 @@ fake.fake_reset()
 c.sigma_from_coeffs(*args)
 assert fake.fake_live() >= live + big + (4 << 20)
 ''')
+
+
+VJP = '''
+def vjp(c, length, n_omega, n_range):
+    om, g = np.linspace(-5, 5, n_omega), np.ones((1, n_omega, 2))
+    q, sig = np.zeros(1, np.int32), np.zeros((1, n_omega, 2))
+    ge, go = np.zeros(c.n_orb), np.zeros((c.n_orb, c.n_r))
+    return L.gwl_sigma_c_range_vjp(c._h, G._ptr(q), 1, *n_range, G._ptr(om), n_omega, 0.1, length,
+                                   G._ptr(g), G._ptr(sig), G._ptr(ge), G._ptr(go))
+'''
+
+
+def test_kept_gradient_buffers_make_way(fake):
+    """With the card full but for what a gradient call left behind, a call that
+    needs that memory gets it; a second gradient as well, whatever its shape."""
+    run(fake, VJP + '''
+c = context(3, 5, (4, 6, 4))
+assert call("gwl_apply_c", c, 1) == 0
+bare = fake.fake_live()
+assert vjp(c, 6, 50, (0, 8)) == 0
+assert call("gwl_apply_c", c, 8) == 0   # (the products' buffers of that call)
+kept = fake.fake_live()
+fake.fake_limit(kept + 1000)
+assert call("gwl_apply_c", c, 9) == 0
+assert fake.fake_live() < kept + 1000
+
+c = context(3, 5, (4, 6, 4))
+assert vjp(c, 3, 400, (0, 8)) == 0
+fake.fake_reset()
+fake.fake_limit(fake.fake_live() + 1000)
+assert vjp(c, 9, 50, (0, 8)) == 0
+''')
