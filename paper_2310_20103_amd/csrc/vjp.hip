@@ -262,7 +262,6 @@ gwl_status vjp_once(gwl_ctx* ctx, VjpMode mode, const int* qp_states, int n_qp, 
     nbar.ensure_zero(P, st);
     ebar.ensure_zero(P, st);
     sig.ensure_zero((size_t)P * n_omega * 2, st);
-    Gd.ensure((size_t)n_qp * n_omega * 2);
     e_d.ensure(P);
     eta_d.ensure(P);
     om_d.ensure(n_omega);
@@ -278,9 +277,13 @@ gwl_status vjp_once(gwl_ctx* ctx, VjpMode mode, const int* qp_states, int n_qp, 
     }
     // (the forward-only call runs the continued-fraction adjoint for Sigma alone,
     // with a zero cotangent)
-    if (!fwd_only)
+    if (fwd_only) {
+      Gd.ensure_zero((size_t)n_qp * n_omega * 2, st);
+    } else {
+      Gd.ensure((size_t)n_qp * n_omega * 2);
       GWL_HIP(hipMemcpy(Gd.p, grad_sigma, sizeof(double) * n_qp * n_omega * 2,
                         hipMemcpyHostToDevice));
+    }
     GWL_HIP(hipMemcpy(e_d.p, en.data(), sizeof(double) * P, hipMemcpyHostToDevice));
     GWL_HIP(hipMemcpy(eta_d.p, et.data(), sizeof(double) * P, hipMemcpyHostToDevice));
     GWL_HIP(hipMemcpy(om_d.p, om.data(), sizeof(double) * n_omega, hipMemcpyHostToDevice));

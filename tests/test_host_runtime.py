@@ -164,3 +164,17 @@ fake.fake_reset()
 fake.fake_limit(fake.fake_live() + 1000)
 assert vjp(c, 9, 50, (0, 8)) == 0
 ''')
+
+
+def test_forward_alone_has_a_zero_cotangent(fake):
+    """Also after a gradient call whose cotangent is still in the kept buffer."""
+    run(fake, VJP + '''
+c = context(3, 5, (4, 6, 4))
+fake.fake_watch(b"cf_adjoint_kernel", 11, 2 * 40)
+assert vjp(c, 4, 40, (0, 8)) == 0
+assert fake.fake_watched() == 1.0
+fake.fake_watch(b"cf_adjoint_kernel", 11, 2 * 40)
+c.sigma_c_vjp_forward.__func__.__globals__["_sync_torch"] = lambda: None
+c.sigma_c_vjp_forward([0], np.linspace(-5, 5, 40), 0.1, 4)
+assert fake.fake_watched() == 0.0
+''')
