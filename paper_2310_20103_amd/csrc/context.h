@@ -348,18 +348,61 @@ struct gwl_ctx {
     return g;
   }
 
+  // The GEMMs that a call runs: both in the K product, one of them in a
+  // component call or a coupling vector (those are always on the grid).
+  enum Gemms { kFirst = 1, kSecond = 2, kBoth = 3 };
+  const GemmDims& dims_of(Gemms g) const { return g == kBoth ? kd() : gd; }
   // FP64 products of nb vectors on the pair-density GEMMs (compact operands)?
-  bool pd(int nb) const { return fp64_kernel == 1 && gemm_pd_wins(kd(), nb); }
-  // the geometry and buffer of the FP64 operands of nb vectors' K product
-  PairGeom geom64(int nb, bool a_op = false) const {
+  // Where their modelled time is below 97 % of the row GEMMs': padding decides on
+  // the grid (64 vectors, 32^3, 32 + 128 orbitals: 631 us a C product against
+  // 1,120), the length of the first one's chain on few points (64 vectors, 640
+  // points, 35 + 248 orbitals: 371 against 130).  Over 1,883 shapes (128 to
+  // 262,144 points, 3 + 5 to 128 + 512 orbitals, 1 to 256 vectors) the choice is
+  // more than 5 % from the better C product on 9 (8 % at most), and on none of the
+  // 1,328 with up to 64 vectors slower than the row GEMMs alone were before the
+  // pair form was there.
+  bool pd(int nb, Gemms g = kBoth) const {
+    if (fp64_kernel != 1) return false;
+    const GemmDims& d = dims_of(g);
+    if (form.nb == nb && form.gemms == g && form.nrp == d.nrp && form.isdf == isdf_on)
+      return form.pair;
+    double pair = 0, rows = 0;
+    if (g & kFirst) {
+      pair += gemm1_pd_us(d, nb);
+      rows += gemm1_f64m_us(d, nb);
+    }
+    if (g & kSecond) {
+      pair += gemm2_pd_us(d, nb);
+      rows += gemm2_f64m_us(d, nb, row_splitk(nb, d));
+    }
+    // partial densities of further v tiles: read once more by the transform, one
+    // more library product on the ISDF points
+    if (g == kBoth)
+      rows += (gemm1_f64m_vtiles(d) - 1) *
+              (isdf_on ? 12.0 + 0.014 * d.nrp : (double)nb * d.nrp * 8.0 / 4.8e6);
+    form.nb = nb;
+    form.gemms = g;
+    form.nrp = d.nrp;
+    form.isdf = isdf_on;
+    form.pair = pair < 0.97 * rows;
+    return form.pair;
+  }
+  // the last choice (a product asks several times)
+  struct Form {
+    int nb = -1, gemms = 0, nrp = 0, isdf = 0;
+    bool pair = false;
+  };
+  mutable Form form;
+  // the geometry and buffer of the FP64 operands of nb vectors
+  PairGeom geom64(int nb, bool a_op = false, Gemms gemms = kBoth) const {
     PairGeom g = pair_geom(a_op);
-    if (pd(nb)) {
+    if (pd(nb, gemms)) {
       g.nvp = nv;
       g.ncp = nc;
     }
     return g;
   }
-  double* ubuf64(int nb) const { return pd(nb) ? u64c.p : u64.p; }
+  double* ubuf64(int nb, Gemms g = kBoth) const { return pd(nb, g) ? u64c.p : u64.p; }
 
   int nvt_max() const {
     return std::max(std::max(gemm1_f64_vtiles(gd), gemm1_f16s_vtiles(gd)),
@@ -367,39 +410,41 @@ struct gwl_ctx {
   }
 
   // Split of the grid sum in the second GEMM.
-  int auto_splitk(int nb, int prec) const {
+  int auto_splitk(int nb, int prec, Gemms g = kBoth) const {
     if (splitk > 0) return splitk;
     const bool model = prec == GWL_FP64 && fp64_kernel;  // (these kernels' rules need no tuning)
     if (!model && tuned[prec].B == nb && tuned[prec].S > 0) return tuned[prec].S;
-    return heuristic_splitk(nb, prec, kd());
+    return heuristic_splitk(nb, prec, g);
   }
-  int heuristic_splitk(int nb, int prec, const GemmDims& d) const {
-    if (prec == GWL_FP64 && pd(nb)) return gemm2_pd_split(d, nb);
-    if (fp64_kernel && prec == GWL_FP64) {
-      // The split that a model of the FP64 kernel's time prefers: a CU works
-      // through its blocks at 1.9 us per K step of 16 (64 matrix instructions
-      // per SIMD; 8 % more when one block has the CU to itself), each block
-      // costs about five more steps, and every partial tile is written and
-      // read once.  It picks the best measured split where tried: 12 vectors of
-      // 64 + 256 orbitals at 48^3 42 of {16, 21, 32, 42}, 64 vectors 8 of {4, 8,
-      // 16, 24}, on 1,280 ISDF points 4 of {1..6, 8}.
-      const long tiles = gemm2_f64m_blocks(d, nb);
-      const int smax = (int)std::max<long>(1, std::min<long>(max_splitk(nb), d.nrp / 128));
-      int best = 1;
-      double least = 1e300;
-      for (int s = 1; s <= smax; ++s) {
-        const long per_cu = ceil_div(tiles * s, 256);
-        const double us = per_cu * (ceil_div(d.nrp, 16L * s) + 5) * 1.9 * (per_cu == 1 ? 1.08 : 1.0) +
-                          s * tiles * (2.0 * 128 * 128 * 8 / 4.8e6);
-        if (us < least) {
-          least = us;
-          best = s;
-        }
-      }
-      return best;
-    }
+  int heuristic_splitk(int nb, int prec, Gemms g = kBoth) const {
+    const GemmDims& d = dims_of(g);
+    if (prec == GWL_FP64 && pd(nb, g)) return gemm2_pd_split(d, nb);
+    if (fp64_kernel && prec == GWL_FP64) return row_splitk(nb, d);
     if (fp64_kernel && !tuning) return model16(nb, d, tile16(nb)).second;
     return fill_splitk(nb, d);
+  }
+  // The split that a model of the FP64 row kernel's time prefers: a CU works
+  // through its blocks at 1.9 us per K step of 16 (64 matrix instructions
+  // per SIMD; 8 % more when one block has the CU to itself), each block
+  // costs about five more steps, and every partial tile is written and
+  // read once.  It picks the best measured split where tried: 12 vectors of
+  // 64 + 256 orbitals at 48^3 42 of {16, 21, 32, 42}, 64 vectors 8 of {4, 8,
+  // 16, 24}, on 1,280 ISDF points 4 of {1..6, 8}.
+  int row_splitk(int nb, const GemmDims& d) const {
+    const long tiles = gemm2_f64m_blocks(d, nb);
+    const int smax = (int)std::max<long>(1, std::min<long>(max_splitk(nb), d.nrp / 128));
+    int best = 1;
+    double least = 1e300;
+    for (int s = 1; s <= smax; ++s) {
+      const long per_cu = ceil_div(tiles * s, 256);
+      const double us = per_cu * (ceil_div(d.nrp, 16L * s) + 5) * 1.9 * (per_cu == 1 ? 1.08 : 1.0) +
+                        s * tiles * (2.0 * 128 * 128 * 8 / 4.8e6);
+      if (us < least) {
+        least = us;
+        best = s;
+      }
+    }
+    return best;
   }
   // Split that fills the chip (about 1024 blocks) while each split keeps >= 512
   // grid points: the plain FMA tiles', where the autotuner starts, and the least
@@ -515,7 +560,7 @@ struct gwl_ctx {
   // rho <- the first GEMM with its fused row-dot for nb vectors (u already
   // cast): partial densities [nvt][nb][N_rp] in the working precision (FP64,
   // or FP32 carrying the scales u_scale * orb16_scale^2); returns nvt.
-  int first_gemm(int nb, int prec) {
+  int first_gemm(int nb, int prec, Gemms g = kBoth) {
     hipStream_t st = stream;
     const bool is = isdf_on;
     const GemmDims& d = kd();
@@ -526,7 +571,7 @@ struct gwl_ctx {
       const double* vrv = is ? ipsi_v_rv64.p : psi_v_rv64.p;
       const double* pt = is ? ipsi_t.p : psi_t.p;
       double* rp = reinterpret_cast<double*>(rho.p);
-      if (pd(nb)) {
+      if (pd(nb, g)) {
         gemm1_pd(d, nb, pt, pt + (size_t)d.nvp * d.nrp, u64c.p, rp, st);
         nvt = 1;
       } else if (fp64_kernel) {
@@ -608,8 +653,8 @@ struct gwl_ctx {
   }
 
   void second_gemm64(const GemmDims& d, int nb, int S, const double* pv, const double* pc,
-                     const double* v, double* y) {
-    if (pd(nb))
+                     const double* v, double* y, Gemms g = kBoth) {
+    if (pd(nb, g))
       gemm2_pd(d, nb, S, pv, pc, v, y, stream);
     else if (fp64_kernel)
       gemm2_f64m(d, nb, S, pv, pc, v, y, stream);
@@ -635,9 +680,9 @@ struct gwl_ctx {
                            reinterpret_cast<cplx<double>*>(fftx.p), stream);
   }
 
-  void cast(int nb, const double* x, int prec, bool a_op = false) {
+  void cast(int nb, const double* x, int prec, bool a_op = false, Gemms gemms = kBoth) {
     if (prec == GWL_FP64) {
-      cast_u<double>(geom64(nb, a_op), nb, x, nvc, ubuf64(nb), stream);
+      cast_u<double>(geom64(nb, a_op, gemms), nb, x, nvc, ubuf64(nb, gemms), stream);
     } else {
       PairGeom g = pair_geom(a_op);
       g.uscale = u_scale;
@@ -730,12 +775,12 @@ struct gwl_ctx {
       poisson_launch<double>(pg64, rp, gd.nrp, 0, 1, vp, gd.nrp, cnt, fx, stream);
     }
     // (the coupling integrals stay on the grid when the K product is on the points)
-    const int S = isdf_on && !splitk ? heuristic_splitk(cnt, GWL_FP64, gd)
-                                     : auto_splitk(cnt, GWL_FP64);
+    const int S = isdf_on && !splitk ? heuristic_splitk(cnt, GWL_FP64, kSecond)
+                                     : auto_splitk(cnt, GWL_FP64, kSecond);
     const double* pv = psi_t.p;
     const double* pc = psi_t.p + (size_t)gd.nvp * gd.nrp;
-    second_gemm64(gd, cnt, S, pv, pc, vp, yp);
-    coupling_finish<double>(geom64(cnt, tda != 0), cnt, S, yp, dst, ldp, stream);
+    second_gemm64(gd, cnt, S, pv, pc, vp, yp, kSecond);
+    coupling_finish<double>(geom64(cnt, tda != 0, kSecond), cnt, S, yp, dst, ldp, stream);
   }
 
   // w = p_g(C) q over nb slots; replays a captured graph of the whole product
@@ -868,7 +913,7 @@ struct gwl_ctx {
         for (int B : cands) {
           if (B > bmax && B != cands[0]) break;
           ensure_work(B, 1, false);
-          const int s0 = heuristic_splitk(B, prec, kd());
+          const int s0 = heuristic_splitk(B, prec);
           const bool model = prec == GWL_FP64 && fp64_kernel;
           for (int S : {s0 / 2, s0, s0 * 2}) {
             if (model && S != s0) continue;
@@ -902,7 +947,7 @@ struct gwl_ctx {
       best.tile = tiles[0];
       bf16_tile = best.tile;
       best.B = std::max(1, std::min(bmax, 128));
-      best.S = heuristic_splitk(best.B, prec, kd());
+      best.S = heuristic_splitk(best.B, prec);
       best.us_per_vec = 0;
     }
     set_tile(best.tile);

@@ -937,4 +937,20 @@ int gemm2_f64m_blocks(const GemmDims& d, int nb) {
   return ceil_div(nb * d.nvp, DM) * ceil_div(d.ncp, DN);
 }
 
+// Times of the FP64 row GEMMs: a CU works through its blocks at 1.75 to 1.9 us
+// per K step of 16 (64 matrix instructions per SIMD); a block costs 2.7 or 4
+// more steps.  The first one's count is the largest of an XCD (the tile map
+// leaves blocks of the grid empty).  Against 1,405 shapes (128 to 262,144
+// points, 3 + 5 to 128 + 512 orbitals, 1 to 256 vectors) 5 % rms where the
+// choice of form is open.
+double gemm1_f64m_us(const GemmDims& d, int nb) {
+  const long per_cu = ceil_div(gemm1_grid(ceil_div((long)nb * d.nvp, DM), d.nrp / DN), 256);
+  return 9.3 + per_cu * (d.ncp / DK + 2.7) * 1.75;
+}
+double gemm2_f64m_us(const GemmDims& d, int nb, int splitk) {
+  const long per_cu = ceil_div((long)gemm2_f64m_blocks(d, nb) * splitk, 256);
+  const long steps = round_up(ceil_div(d.nrp, splitk), 2 * DK) / DK;
+  return per_cu * (steps + 4) * 1.9 * (per_cu == 1 ? 1.15 : 1.0);
+}
+
 }  // namespace gwl

@@ -20,9 +20,11 @@
 // wide instead of four column blocks, and add their sums through LDS in a
 // fixed order.
 //
-// Bound by the matrix cores once a CU holds two blocks.  Against the (b, v)-row
-// kernels: 64 vectors, 32^3, 32 + 128 orbitals: 680 -> 333 us (51 TFLOP/s) and
-// 582 -> 290 us (59); 80 vectors, 24^3, 8 + 32: 234 -> 20 and 479 -> 21 us.
+// Bound by the matrix cores once a CU holds two blocks.  Rows and pairs on one
+// card: 64 vectors, 32^3, 32 + 128 orbitals 572 and 322 us (53 TFLOP/s), 492 and
+// 280 (61); 80 vectors, 24^3, 8 + 32: 211 and 24 us, 279 and 27.  Few points and
+// many pairs are the rows' (gwl_ctx::pd): 64 vectors on 640 points, 35 + 248
+// orbitals, 84 and 318 us for both.
 #include <algorithm>
 
 #include "common.h"
@@ -423,24 +425,66 @@ size_t gemm_pd_u_size(int nb, long nvc) {
   return (size_t)(nb + 16 * pd_mt(nb)) * nvc;  // whole M tiles
 }
 
-bool gemm_pd_wins(const GemmDims& d, int nb) {
-  // Matrix instructions issued per useful one, of both GEMMs: here the batch
-  // padded to 16; there N_v to N_vp and N_c to N_cp (first) or 128 (second).
-  // Where both are full (64 vectors, 64 + 256 orbitals) the (b, v) rows reach
-  // the same rate from wider tiles and stay; one vector of 8 + 32 orbitals
-  // (1/16 against 1/24) takes 21 us here and 162 us there.
-  const double here = 2.0 * 16.0 * pd_mt(nb) * pd_mi(nb) / nb;
-  const double there = (double)d.nvp / d.nv * ((double)d.ncp + (double)round_up(d.ncp, 128)) / d.nc;
-  return here < there;
-}
+namespace {
 
 // Blocks of the second GEMM aimed at: two per CU.  K shares inside the block
 // while 32 splits of the grid sum cannot give them.
-static int pd2_shares(const GemmDims& d, int nb) {
+int pd2_shares(const GemmDims& d, int nb) {
   const long nvc = (long)d.nv * d.nc, smax = std::min<long>(32, std::max(1, d.nrp / 128));
   for (int kg : {1, 2})
     if ((long)pd_mt(nb) * ceil_div(nvc, 64 / kg) * smax >= 384) return kg;
   return 4;
+}
+
+// Column blocks per wave and K shares of a launch: PdTile's NJ and KG.
+struct PdShape {
+  int nj, kg;
+  int columns() const { return 64 * nj / kg; }
+};
+PdShape pd1_shape(const GemmDims& d, int nb) {
+  const long blocks = (long)pd_mt(nb) * (d.nrp / 64);
+  if (blocks >= 1024) return {2, 1};
+  return {1, blocks >= 384 ? 1 : blocks >= 192 ? 2 : 4};
+}
+PdShape pd2_shape(const GemmDims& d, int nb, int splitk) {
+  const int kg = pd2_shares(d, nb);
+  const long nvc = (long)d.nv * d.nc;
+  return {kg == 1 && (long)pd_mt(nb) * ceil_div(nvc, 128) * splitk >= 512 ? 2 : 1, kg};
+}
+
+// Time (us) of `blocks` blocks of K steps of kb on 256 CUs, two to a CU: the CU
+// is busy with both blocks' matrix instructions (`mma` each, per wave), or a block
+// waits for its own chain of barrier and loads, `lat` a step.
+double pd_us(long blocks, const PdShape& s, int mi, int kb, double steps, double mma, double lat) {
+  const double per_cu = ceil_div(blocks, 256), both = std::min(per_cu, 2.0);
+  const double m = mma * mi * s.nj * (kb / 4) / s.kg;
+  return per_cu / both * steps * std::max(both * m, m + lat);
+}
+
+}  // namespace
+
+// Times of both GEMMs, fitted like those of the row GEMMs (9 and 11 % rms).  The
+// first has no split of K: its chain of N_v N_c / KB steps is what few columns
+// and many pairs wait for (640 points, 30 + 120 orbitals, 64 vectors: 123 us, the
+// row GEMM 30).  From 2^18 points on, rows 2 MB apart, the second is 10 to 40 %
+// slower than its blocks say.
+double gemm1_pd_us(const GemmDims& d, int nb) {
+  const PdShape s = pd1_shape(d, nb);
+  const int mi = pd_mi(nb), kb = pd_kb(mi, s.nj, s.kg, 32);
+  const double mma = s.nj == 2 ? 0.034 : s.kg == 1 ? 0.038 : s.kg == 2 ? 0.044 : 0.0545;
+  const long blocks = (long)pd_mt(nb) * (d.nrp / s.columns());
+  const int ncf = d.nv > 1 ? d.nc / kb * kb : 0;
+  return 5.0 + pd_us(blocks, s, mi, kb, round_up((long)ncf / kb * d.nv, 2), mma, 0.32) +
+         pd_us(blocks, s, mi, kb, ceil_div((long)d.nv * (d.nc - ncf), kb), mma, 0.49);
+}
+double gemm2_pd_us(const GemmDims& d, int nb) {
+  const int splitk = gemm2_pd_split(d, nb);
+  const PdShape s = pd2_shape(d, nb, splitk);
+  const int mi = pd_mi(nb), kb = pd_kb(mi, s.nj, s.kg, 64);
+  const long chunk = round_up(ceil_div(d.nrp, splitk), 128);
+  const long blocks = (long)pd_mt(nb) * ceil_div((long)d.nv * d.nc, s.columns()) * ceil_div(d.nrp, chunk);
+  return (6.0 + pd_us(blocks, s, mi, kb, chunk / kb, 0.035, 0.32 + 0.16 * kb / 16)) *
+         (d.nrp >= 1 << 18 ? 1.1 : 1.0);
 }
 
 int gemm2_pd_split(const GemmDims& d, int nb) {
@@ -470,12 +514,12 @@ void gemm1_pd(const GemmDims& d, int nb, const double* psi_v_t, const double* ps
   gemm1_pd_kernel<MIV, NJV, KGV>                                                           \
       <<<pd_grid((long)mt * (d.nrp / (64 * NJV / KGV))), NT, 0, st>>>(            \
           d, nvc, nb, mt, psi_v_t, psi_c_t, u, rho)
-  const long blocks = (long)mt * (d.nrp / 64);
-  if (blocks >= 1024) {
+  const PdShape s = pd1_shape(d, nb);
+  if (s.nj == 2) {
     GWL_PD_MI(2, 1)
-  } else if (blocks >= 384) {
+  } else if (s.kg == 1) {
     GWL_PD_MI(1, 1)
-  } else if (blocks >= 192) {
+  } else if (s.kg == 2) {
     GWL_PD_MI(1, 2)
   } else {
     GWL_PD_MI(1, 4)
@@ -496,12 +540,12 @@ void gemm2_pd(const GemmDims& d, int nb, int splitk, const double* psi_v_t,
     gemm2_pd_kernel<MIV, NJV, KGV><<<pd_grid((long)mt * nt * splitk), NT, 0, st>>>(        \
         d, nvc, nb, mt, nt, splitk, kchunk, psi_v_t, psi_c_t, vpot, ypart);                \
   } while (0)
-  const int kg = pd2_shares(d, nb);
-  if (kg == 1 && (long)mt * ceil_div(nvc, 128) * splitk >= 512) {
+  const PdShape s = pd2_shape(d, nb, splitk);
+  if (s.nj == 2) {
     GWL_PD_MI(2, 1)
-  } else if (kg == 1) {
+  } else if (s.kg == 1) {
     GWL_PD_MI(1, 1)
-  } else if (kg == 2) {
+  } else if (s.kg == 2) {
     GWL_PD_MI(1, 2)
   } else {
     GWL_PD_MI(1, 4)

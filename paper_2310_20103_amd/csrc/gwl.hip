@@ -626,8 +626,8 @@ gwl_status gwl_pair_density(gwl_ctx* ctx, const double* x, double* rho, int n_ve
     const GemmDims& d = ctx->gd;
     for (int i0 = 0; i0 < n_vec; i0 += chunk) {
       const int nb = std::min(chunk, n_vec - i0);
-      ctx->cast(nb, x + (size_t)i0 * ctx->nvc, precision);
-      const int nvt = ctx->first_gemm(nb, precision);
+      ctx->cast(nb, x + (size_t)i0 * ctx->nvc, precision, false, gwl_ctx::kFirst);
+      const int nvt = ctx->first_gemm(nb, precision, gwl_ctx::kFirst);
       dim3 grid((unsigned)std::min<long>(1024, (ctx->nr + 255) / 256), (unsigned)nb);
       double* out = rho + (size_t)i0 * ctx->nr;
       if (precision == GWL_FP64) {
@@ -667,7 +667,7 @@ gwl_status gwl_potential_product(gwl_ctx* ctx, const double* v, double* y, int n
       const int nb = std::min(chunk, n_vec - i0);
       const double* vb = v + (size_t)i0 * c.nr;
       double* yb = y + (size_t)i0 * c.nvc;
-      const int S = c.auto_splitk(nb, precision);
+      const int S = c.auto_splitk(nb, precision, gwl_ctx::kSecond);
       dim3 gr((unsigned)std::min<long>(1024, (d.nrp + 255) / 256), (unsigned)nb);
       dim3 gy((unsigned)std::min<long>(1024, (c.nvc + 255) / 256), (unsigned)nb);
       c.prof_begin();
@@ -676,8 +676,8 @@ gwl_status gwl_potential_product(gwl_ctx* ctx, const double* v, double* y, int n
         const double* pv = c.psi_t.p;
         const double* pc = c.psi_t.p + (size_t)d.nvp * d.nrp;
         double* yp = reinterpret_cast<double*>(c.ypart.p);
-        c.second_gemm64(d, nb, S, pv, pc, c.vpot64.p, yp);
-        const PairGeom g = c.geom64(nb);
+        c.second_gemm64(d, nb, S, pv, pc, c.vpot64.p, yp, gwl_ctx::kSecond);
+        const PairGeom g = c.geom64(nb, false, gwl_ctx::kSecond);
         potprod_finish_kernel<double><<<gy, 256, 0, st>>>(c.nv, c.nc, g.nvp, g.ncp, nb, S, yp,
                                                           nullptr, c.dv, yb);
       } else {

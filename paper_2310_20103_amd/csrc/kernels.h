@@ -131,13 +131,15 @@ void gemm1_f64m(const GemmDims& d, int nb, const double* psi_c_rc, const double*
                 const double* u, double* rho_part, hipStream_t st);
 void gemm2_f64m(const GemmDims& d, int nb, int splitk, const double* psi_v_t,
                 const double* psi_c_t, const double* vpot, double* ypart, hipStream_t st);
+double gemm1_f64m_us(const GemmDims& d, int nb);  // modelled times (us)
+double gemm2_f64m_us(const GemmDims& d, int nb, int splitk);
 
 // FP64 on MFMA with the pair densities phi_v phi_c as the operand: u, ypart
 // compact ([b][N_v N_c], [S][b][N_v N_c]), one density per vector (one v
-// tile).  gemm_pd_wins: whether this batch pads less than gemm1_f64m /
-// gemm2_f64m; gemm2_pd_split: blocks per batch against grid points per block.
+// tile).  gemm2_pd_split: blocks per batch against grid points per block.
 // gemm_pd_u_size: doubles to allocate for u (its rows are read past the batch).
-bool gemm_pd_wins(const GemmDims& d, int nb);
+double gemm1_pd_us(const GemmDims& d, int nb);  // modelled times (us)
+double gemm2_pd_us(const GemmDims& d, int nb);  // (at gemm2_pd_split)
 size_t gemm_pd_u_size(int nb, long nvc);
 int gemm2_pd_split(const GemmDims& d, int nb);
 void gemm1_pd(const GemmDims& d, int nb, const double* psi_v_t, const double* psi_c_t,

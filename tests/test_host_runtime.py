@@ -15,7 +15,7 @@ LIB = os.path.join(ROOT, "paper_2310_20103_amd", "_lib", "libgwl.so")
 pytestmark = pytest.mark.skipif(not os.path.exists(LIB), reason="libgwl.so not built")
 
 PREAMBLE = '''
-import ctypes as ct, importlib.util, sys
+import ctypes as ct, importlib.util, re, sys
 import numpy as np
 fake = ct.CDLL(sys.argv[1], mode=ct.RTLD_GLOBAL)
 fake.fake_log.restype = ct.c_char_p
@@ -49,6 +49,12 @@ def call(name, c, n_vec, *a):
              "gwl_pair_density": (c.n_vc, c.n_r), "gwl_potential_product": (c.n_r, c.n_vc)}[name]
     x, y = np.zeros((n_vec, width[0])), np.zeros((n_vec, width[1]))
     return getattr(L, name)(c._h, G._ptr(x), G._ptr(y), n_vec, *(a or (0,)))
+
+def gemms():
+    """The FP64 GEMM launches in the log: [("gemm1_pd", "1", "2", "1"), ("gemm2_f64m",), ...]"""
+    return [tuple(x for x in m if x)
+            for m in re.findall(r"(gemm[12]_(?:pd|f64m))_kernel(?:ILi(\\d+)ELi(\\d+)ELi(\\d+)E)?",
+                                "\\n".join(log()))]
 '''
 
 
@@ -177,4 +183,28 @@ fake.fake_watch(b"cf_adjoint_kernel", 11, 2 * 40)
 c.sigma_c_vjp_forward.__func__.__globals__["_sync_torch"] = lambda: None
 c.sigma_c_vjp_forward([0], np.linspace(-5, 5, 40), 0.1, 4)
 assert fake.fake_watched() == 0.0
+''')
+
+
+@pytest.mark.parametrize("grid,nv,nc,n,form", [
+    # measured C products (us): rows, pairs
+    ((12, 12, 12), 100, 300, 33, "f64m"),   # 281, 1,095
+    ((18, 16, 18), 64, 200, 64, "f64m"),    # 431, 655
+    ((36, 32, 32), 76, 171, 8, "f64m"),     # 525, 806
+    ((32, 32, 32), 87, 139, 8, "f64m"),     # 523, 789
+    ((24, 24, 24), 8, 32, 1, "pd"),         # 90, 52
+    ((24, 24, 24), 8, 32, 64, "pd"),
+    ((32, 32, 32), 32, 128, 64, "pd"),      # 1,120, 631
+])
+def test_form_of_the_product(fake, grid, nv, nc, n, form):
+    """Pair densities as the GEMM operand where that is the faster product, and
+    both halves of a K product in one form."""
+    run(fake, f'''
+c = context({nv}, {nc}, {grid})
+assert call("gwl_apply_c", c, {n}) == 0
+assert {{k[0] for k in gemms()}} == {{"gemm1_{form}", "gemm2_{form}"}}, gemms()
+c.set_option(G.KEY_KERNELS, 0)
+fake.fake_reset()
+assert call("gwl_apply_c", c, {n}) == 0
+assert not gemms()
 ''')
