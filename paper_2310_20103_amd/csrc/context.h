@@ -444,7 +444,7 @@ struct gwl_ctx {
         best = s;
       }
     }
-    return best;
+    return full_splits(d.nrp, best, kUnit64);
   }
   // Split that fills the chip (about 1024 blocks) while each split keeps >= 512
   // grid points: the plain FMA tiles', where the autotuner starts, and the least
@@ -477,6 +477,7 @@ struct gwl_ctx {
                         (double)s * nb * d.nvp * d.ncp * 8.0 / 4.8e6;
       if (us < best.first) best = {us, s};
     }
+    best.second = full_splits(d.nrp, best.second, kUnit16);
     return best;
   }
   // Block tile of the mixed second GEMM for nb vectors: the caller's, the tuned

@@ -873,7 +873,8 @@ void gemm2_f64m(const GemmDims& d, int nb, int splitk, const double* psi_v_t,
                 const double* psi_c_t, const double* vpot, double* ypart, hipStream_t st) {
   if (nb <= 0) return;
   const int M = nb * d.nvp;
-  const int kchunk = (int)round_up(ceil_div(d.nrp, splitk), 2 * DK);
+  static_assert(kUnit64 == 2 * DK, "two K steps");
+  const int kchunk = split_chunk(d.nrp, splitk, kUnit64);
   const int blocks = ceil_div(M, DM) * ceil_div(d.ncp, DN) * splitk;
   gemm2_f64m_kernel<<<blocks, 256, 0, st>>>(d, M, splitk, kchunk, psi_v_t, psi_c_t, vpot, ypart);
   GWL_HIP(hipGetLastError());
@@ -904,7 +905,8 @@ void gemm2_f16(const GemmDims& d, int nb, int bn, int splitk, const f16_t* psi_v
                const f16_t* psi_c_t, const f16_t* vpot, float* ypart, hipStream_t st) {
   if (nb <= 0) return;
   const int M = nb * d.nvp;
-  const int kchunk = (int)round_up(ceil_div(d.nrp, splitk), 2 * HK);
+  static_assert(kUnit16 == 2 * HK, "two K steps");
+  const int kchunk = split_chunk(d.nrp, splitk, kUnit16);
   const int blocks = gemm2_f16_blocks(d, nb, bn) * splitk;
   const bool panel = orb16_panel_halves(d) != 0;
 #define GWL_G2(BNV, NVPV)                                                                    \
@@ -949,7 +951,7 @@ double gemm1_f64m_us(const GemmDims& d, int nb) {
 }
 double gemm2_f64m_us(const GemmDims& d, int nb, int splitk) {
   const long per_cu = ceil_div((long)gemm2_f64m_blocks(d, nb) * splitk, 256);
-  const long steps = round_up(ceil_div(d.nrp, splitk), 2 * DK) / DK;
+  const long steps = split_chunk(d.nrp, splitk, kUnit64) / DK;
   return per_cu * (steps + 4) * 1.9 * (per_cu == 1 ? 1.15 : 1.0);
 }
 

@@ -481,16 +481,17 @@ double gemm2_pd_us(const GemmDims& d, int nb) {
   const int splitk = gemm2_pd_split(d, nb);
   const PdShape s = pd2_shape(d, nb, splitk);
   const int mi = pd_mi(nb), kb = pd_kb(mi, s.nj, s.kg, 64);
-  const long chunk = round_up(ceil_div(d.nrp, splitk), 128);
-  const long blocks = (long)pd_mt(nb) * ceil_div((long)d.nv * d.nc, s.columns()) * ceil_div(d.nrp, chunk);
-  return (6.0 + pd_us(blocks, s, mi, kb, chunk / kb, 0.035, 0.32 + 0.16 * kb / 16)) *
+  const long blocks = (long)pd_mt(nb) * ceil_div((long)d.nv * d.nc, s.columns()) * splitk;
+  return (6.0 + pd_us(blocks, s, mi, kb, split_chunk(d.nrp, splitk, kUnitPd) / kb, 0.035,
+                      0.32 + 0.16 * kb / 16)) *
          (d.nrp >= 1 << 18 ? 1.1 : 1.0);
 }
 
 int gemm2_pd_split(const GemmDims& d, int nb) {
   const long nvc = (long)d.nv * d.nc;
   const long tiles = (long)pd_mt(nb) * ceil_div(nvc, 64 / pd2_shares(d, nb));
-  return (int)std::max<long>(1, std::min<long>({512 / tiles, 32, d.nrp / 128}));
+  const long most = std::max<long>(1, std::min<long>({512 / tiles, 32, d.nrp / 128}));
+  return full_splits(d.nrp, (int)most, kUnitPd);
 }
 
 #define GWL_PD_MI(NJV, KGV)                               \
@@ -533,7 +534,7 @@ void gemm2_pd(const GemmDims& d, int nb, int splitk, const double* psi_v_t,
   if (nb <= 0) return;
   const long nvc = (long)d.nv * d.nc;
   const int mt = pd_mt(nb);
-  const int kchunk = (int)round_up(ceil_div(d.nrp, splitk), 128);
+  const int kchunk = split_chunk(d.nrp, splitk, kUnitPd);
 #define GWL_PD(MIV, NJV, KGV)                                                              \
   do {                                                                                     \
     const int nt = ceil_div(nvc, (64 * NJV / KGV));                               \

@@ -108,6 +108,17 @@ __host__ __device__ inline long orb16_index(const GemmDims& d, long row, long r)
   return ph ? (r >> 5) * ph + row * 32 + (r & 31) : row * d.nrp + r;
 }
 
+// The grid sum of the second GEMM in `split` parts: points per part (whole units
+// of the kernel's K steps) and the parts that hold any.
+inline int split_chunk(int nrp, int split, int unit) {
+  return (int)round_up(ceil_div(nrp, split), unit);
+}
+inline int full_splits(int nrp, int split, int unit) {
+  return ceil_div(nrp, split_chunk(nrp, split, unit));
+}
+// units: FP64 rows, FP64 pair densities, FP16
+constexpr int kUnit64 = 32, kUnitPd = 128, kUnit16 = 64;
+
 // FP64 (plain tiled FMA; reference-quality GPU path).
 int gemm1_f64_vtiles(const GemmDims& d);
 void gemm1_f64(const GemmDims& d, int nb, const double* psi_c_rc, const double* psi_v_rv,

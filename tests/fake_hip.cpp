@@ -188,8 +188,12 @@ int __hipPopCallConfiguration(Dim3* g, Dim3* b, size_t* sh, void** st) {
 int hipLaunchKernel(const void* f, Dim3 g, Dim3 b, void** args, size_t, void*) {
   const std::string& name = kernels[f];
   log_text += name + " " + std::to_string(g.x) + " " + std::to_string(g.y) + " " + std::to_string(b.x);
-  if (name.find("gemm2_pd_kernel") != std::string::npos)  // split, points per split
-    log_text += " " + std::to_string(*(int*)args[5]) + " " + std::to_string(*(int*)args[6]);
+  const bool pd = name.find("gemm2_pd_kernel") != std::string::npos;
+  if (pd || name.find("gemm2_f64m_kernel") != std::string::npos ||
+      name.find("gemm2_f16_n") != std::string::npos) {  // split, points per part
+    const int k = pd ? 5 : 2;
+    log_text += " split " + std::to_string(*(int*)args[k]) + " " + std::to_string(*(int*)args[k + 1]);
+  }
   log_text += unsynced ? " unsynced\n" : "\n";
   if (!watch_kernel.empty() && name.find(watch_kernel) != std::string::npos) {
     const double* p = *(const double**)args[watch_arg];

@@ -208,3 +208,21 @@ fake.fake_reset()
 assert call("gwl_apply_c", c, {n}) == 0
 assert not gemms()
 ''')
+
+
+@pytest.mark.parametrize("nv,nc", [(8, 32), (33, 70), (100, 300)])
+@pytest.mark.parametrize("grid", [(4, 6, 4), (12, 12, 8), (18, 18, 18), (24, 24, 24), (16, 27, 18)],
+                         ids=lambda g: "x".join(map(str, g)))
+def test_every_split_holds_points(fake, grid, nv, nc):
+    """No part of the second GEMM's grid sum is empty."""
+    run(fake, f'''
+c = context({nv}, {nc}, {grid})
+n = -(-c.n_r // 256) * 256
+for precision in (G.FP64, G.MIXED_F16):
+    for nb in (1, 5, 16, 31, 33, 64):
+        fake.fake_reset()
+        assert call("gwl_apply_c", c, nb, precision) == 0
+        parts = [tuple(map(int, m)) for m in re.findall(r"split (\\d+) (\\d+)", "\\n".join(log()))]
+        assert parts
+        assert all((s - 1) * k < n <= s * k for s, k in parts), (nb, parts)
+''')
