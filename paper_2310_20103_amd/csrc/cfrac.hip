@@ -125,8 +125,8 @@ interval_check_kernel(int npairs, const double* __restrict__ ca, const double* _
 // applying each plane rotation to the first row of the eigenvector matrix
 // only (Golub and Welsch).  One thread per pair: a serial chain of rotations
 // over d, e and z (FP64), which live in LDS ([k][thread], stride = blockDim.x)
-// where 3 ld doubles for a useful number of threads fit there, and in the pair's
-// rows of the scratch arrays otherwise (80 pairs, L = 30: 1,257 us in the
+// where those of all pairs fit there (quad_sigma), and in the pair's rows of the
+// scratch arrays otherwise (80 pairs, L = 30: 1,257 us in the
 // scratch rows with 64 lanes per wave, 617 us as it is).  On return qd = theta, qz = ||P||^2 u(0)^2.
 // status[p] = 1 if an eigenvalue needed more than 60 sweeps.
 template <typename T>
@@ -297,13 +297,22 @@ void quad_sigma(int npairs, const double* coef_a, const double* coef_b, const in
                 double* qz, int* status, double* sig, hipStream_t st) {
   if (npairs <= 0 || nomega <= 0) return;
   GWL_CHECK(ld <= CF_MAXL, GWL_EINVAL, "Lanczos length exceeds 4000");
-  // threads per block: one while a wave per SIMD is not reached (lanes of a wave
-  // wait for the longest of their sweeps), and no more than fit 64 KB of LDS
-  int nt = 1;
-  while (nt < 64 && ceil_div(npairs, nt) > 1024) nt *= 2;
-  while (nt > 1 && (size_t)nt * 3 * ld * sizeof(double) > 65536) nt /= 2;
-  const size_t lds = (size_t)nt * 3 * ld * sizeof(double);
-  if (lds <= 65536)
+  // In LDS where every block is resident at once: blocks that wait for others to
+  // end cost more than LDS saves (20,000 pairs of 600: 2.58 s in ten rounds, 0.67 s
+  // in the scratch rows; of 200: 112 and 72 ms; 6,400 of 200, all resident, 53 and
+  // 57 ms).  Threads per block: as few as give no more than a wave per SIMD (lanes
+  // of a wave wait for the longest of their sweeps), else as many as fit.
+  auto lds_of = [&](int nt) { return (size_t)nt * 3 * ld * sizeof(double); };
+  int nt = 0;
+  for (int t = 1; t <= 64 && lds_of(t) <= 65536; t *= 2) {
+    const long blocks = ceil_div(npairs, t);
+    const long per_cu = std::min<long>(32, 160 * 1024 / round_up(lds_of(t), 1280));
+    if (blocks > 256 * per_cu) continue;
+    nt = t;
+    if (blocks <= 1024) break;
+  }
+  const size_t lds = lds_of(nt);
+  if (nt > 0)
     quad_eig_kernel<true><<<ceil_div(npairs, nt), nt, lds, st>>>(npairs, coef_a, coef_b, lens,
                                                                  norm2, ld, qd, qe, qz, status);
   else

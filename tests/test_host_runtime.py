@@ -226,3 +226,26 @@ for precision in (G.FP64, G.MIXED_F16):
         assert parts
         assert all((s - 1) * k < n <= s * k for s, k in parts), (nb, parts)
 ''')
+
+
+@pytest.mark.parametrize("n_pairs,length,in_lds", [
+    (1, 4, True), (80, 30, True), (640, 200, True), (6400, 200, True), (50000, 30, True),
+    (200, 2730, True), (513, 2730, False), (3, 2731, False), (10000, 200, False), (20000, 200, False),
+    (20000, 600, False)])
+def test_eigenvalues_in_lds(fake, n_pairs, length, in_lds):
+    """The QL iteration works in LDS where all its blocks are resident at once
+    (160 KB and 32 waves a CU, 256 CUs)."""
+    run(fake, f'''
+c = context(3, 5, (4, 6, 4))
+c.set_quadrature(True)
+a = np.ones(({n_pairs}, {length}))
+c.sigma_from_coeffs(np.zeros({n_pairs}), a, a, a[:, 0], np.full({n_pairs}, {length}), [0.0], 0.1)
+lines = [l for l in log() if "quad_eig_kernel" in l]
+assert len(lines) == 1
+assert ("ILb1E" in lines[0]) == {in_lds}, lines
+if {in_lds}:
+    blocks, _, threads = map(int, lines[0].split()[1:4])
+    assert blocks * threads >= {n_pairs} > (blocks - 1) * threads
+    lds = threads * 3 * {length} * 8
+    assert lds <= 65536 and blocks <= 256 * min(32, 160 * 1024 // lds)
+''')
