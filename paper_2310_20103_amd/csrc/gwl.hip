@@ -734,19 +734,25 @@ gwl_status gwl_sigma_x(gwl_ctx* ctx, const int* qp_states, int n_qp, double* sig
       GWL_CHECK(qp_states[i] >= 0 && qp_states[i] < ctx->n_orb, GWL_EINVAL,
                 "qp state out of range");
     gwl_ctx& c = *ctx;
-    // The products phi_v phi_m of up to 65,536 fields' worth of states in one
-    // list, an even number per state (a packed transform holds two products of
-    // one state; the list of an odd N_v ends in a zero field), in chunks of the
-    // work buffers' size.
+    // The products phi_v phi_m of a group of states in one list, an even number
+    // per state (a packed transform holds two products of one state; the list of
+    // an odd N_v ends in a zero field): up to 65,536 products and 32 MB of energy
+    // shares a group.  In frequency space a chunk of 64 products needs the
+    // transform's scratch alone; on the grid, one state's products theirs.
     const int nv = c.nv, per = nv + (nv & 1);
-    const int group = std::min(n_qp, std::max(1, 65536 / per));
-    const int chunk = (int)std::min<long>((long)group * per, 64);
-    c.ensure_work(chunk, 1, false);
+    const int nblk = product_energy_blocks(c.pg64);
+    const long shares = nblk > 0 ? (long)per / 2 * nblk : (long)nv * kEnergyParts;
+    const int group = (int)std::min<long>(
+        n_qp, std::max<long>(1, std::min<long>(65536 / per, (4 << 20) / shares)));
+    const int chunk = (int)std::min<long>(nblk > 0 ? (long)group * per : nv, 64);
+    if (nblk > 0)
+      c.ensure_fft(chunk);
+    else
+      c.ensure_work(chunk, 1, false);
     c.xe_rows.ensure(2 * (size_t)group * per);
     c.xe_out.ensure(group);
+    c.xe_part.ensure((size_t)group * shares);
     cplx<double>* fx = reinterpret_cast<cplx<double>*>(c.fftx.p);
-    const int nblk = product_energy_blocks(c.pg64);
-    c.xe_part.ensure(nblk > 0 ? (size_t)group * per / 2 * nblk : (size_t)group * nv * kEnergyParts);
     for (int q0 = 0; q0 < n_qp; q0 += group) {
       const int nq = std::min(group, n_qp - q0), total = nq * per;
       std::vector<int> rows(2 * (size_t)total);
@@ -764,7 +770,7 @@ gwl_status gwl_sigma_x(gwl_ctx* ctx, const int* qp_states, int n_qp, double* sig
           product_energies(c.pg64, c.psi_t.p, c.gd.nrp, mr + f0, vr + f0,
                            std::min(chunk, total - f0) / 2, c.xe_part.p + (size_t)(f0 / 2) * nblk,
                            fx, c.stream);
-        sum_rows(c.xe_part.p, (long)(per / 2) * nblk, nq, c.dv, c.xe_out.p, c.stream);
+        sum_rows(c.xe_part.p, shares, nq, c.dv, c.xe_out.p, c.stream);
       } else {
         // sum_r rho V on the grid, state by state
         double* rp = reinterpret_cast<double*>(c.rho.p);
@@ -778,7 +784,7 @@ gwl_status gwl_sigma_x(gwl_ctx* ctx, const int* qp_states, int n_qp, double* sig
             pair_energy(rp, c.vpot64.p, c.gd.nrp, (int)c.nr, cnt,
                         c.xe_part.p + ((size_t)q * nv + v0) * kEnergyParts, c.stream);
           }
-        sum_rows(c.xe_part.p, (long)nv * kEnergyParts, nq, c.dv, c.xe_out.p, c.stream);
+        sum_rows(c.xe_part.p, shares, nq, c.dv, c.xe_out.p, c.stream);
       }
       GWL_HIP(hipMemcpyAsync(sigma_x_out + q0, c.xe_out.p, nq * sizeof(double),
                              hipMemcpyDeviceToHost, c.stream));

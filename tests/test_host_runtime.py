@@ -249,3 +249,27 @@ if {in_lds}:
     lds = threads * 3 * {length} * 8
     assert lds <= 65536 and blocks <= 256 * min(32, 160 * 1024 // lds)
 ''')
+
+
+@pytest.mark.parametrize("grid,in_frequency_space", [((8, 12, 16), True), ((162, 4, 6), False)])
+@pytest.mark.parametrize("nv,states", [(1, 1), (3, 4), (40, 20)])
+def test_exchange_memory(fake, grid, in_frequency_space, nv, states):
+    """Sigma^ex takes the transform's scratch of at most 64 fields, or where it goes
+    by potentials on the grid the buffers of min(N_v, 64) vectors; besides them
+    only lists and energy shares."""
+    run(fake, f'''
+c = context({nv}, 24, {grid})
+before = fake.fake_live()
+c.sigma_x(np.arange({states}))
+used = fake.fake_live() - before
+if {in_frequency_space}:
+    fields = min({states} * ({nv} + {nv} % 2), 64)
+    most = fields // 2 * c.n_r * 16
+else:
+    d = context({nv}, 24, {grid})
+    before = fake.fake_live()
+    assert call("gwl_apply_c", d, {nv}) == 0
+    most = fake.fake_live() - before
+shares = {states} * {nv + 1} * max(12 * 16, 64) * 8
+assert used <= most + shares + 100000, (used, most)
+''')
