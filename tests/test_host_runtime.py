@@ -273,3 +273,34 @@ else:
 shares = {states} * {nv + 1} * max(12 * 16, 64) * 8
 assert used <= most + shares + 100000, (used, most)
 ''')
+
+
+def test_pair_gemm_cases_reach_every_form(fake):
+    """The sizes that test_gpu_pair_variants.py runs launch the pair-density GEMMs
+    in every form of their rules: (column blocks, K shares) and 1 to 8 row
+    blocks, and two M tiles."""
+    pytest.importorskip("torch")
+    from test_gpu_pair_variants import CASES, SLOTS
+    run(fake, f'''
+seen = set()
+for grid, nv, nc, split, counts in {CASES!r}:
+    c = context(nv, nc, grid)
+    c.set_option(G.KEY_GEMM_SPLITK, split)
+    for n in counts:
+        for name in ("gwl_pair_density", "gwl_potential_product"):
+            assert call(name, c, n) == 0
+    seen |= {{(k[0], *map(int, k[1:])) for k in gemms() if "pd" in k[0]}}
+    c.close()
+for g, forms in (("gemm1_pd", [(2, 1), (1, 1), (1, 2), (1, 4)]),
+                 ("gemm2_pd", [(2, 1), (1, 1), (1, 2), (1, 4)])):
+    for f in forms:
+        rows = sorted(k[1] for k in seen if k[0] == g and k[2:] == f)
+        assert rows and rows[0] <= 2 and rows[-1] >= 5, (g, f, rows)
+    assert {{k[1] for k in seen if k[0] == g}} == set(range(1, 9))
+for grid, nv, nc, slots in {SLOTS!r}:
+    c = context(nv, nc, grid, block=slots)
+    c.lanczos_pairs(np.zeros(slots), np.zeros(slots), np.full(slots, 2))
+    rows = -(-slots // 32)
+    assert {{k[0] for k in gemms() if k[1:] and int(k[1]) == rows}} == {{"gemm1_pd", "gemm2_pd"}}, gemms()
+    c.close()
+''')
