@@ -446,11 +446,9 @@ PdShape pd1_shape(const GemmDims& d, int nb) {
   if (blocks >= 1024) return {2, 1};
   return {1, blocks >= 384 ? 1 : blocks >= 192 ? 2 : 4};
 }
-PdShape pd2_shape(const GemmDims& d, int nb, int splitk) {
-  const int kg = pd2_shares(d, nb);
-  const long nvc = (long)d.nv * d.nc;
-  return {kg == 1 && (long)pd_mt(nb) * ceil_div(nvc, 128) * splitk >= 512 ? 2 : 1, kg};
-}
+// (one column block per wave: two were 5 to 30 % slower from 33 vectors on, 8 to
+// 12 % faster up to 16; 40 vectors, 24^3, 300 + 300 orbitals: 2,351 and 2,939 us)
+PdShape pd2_shape(const GemmDims& d, int nb) { return {1, pd2_shares(d, nb)}; }
 
 // Time (us) of `blocks` blocks of K steps of kb on 256 CUs, two to a CU: the CU
 // is busy with both blocks' matrix instructions (`mma` each, per wave), or a block
@@ -479,7 +477,7 @@ double gemm1_pd_us(const GemmDims& d, int nb) {
 }
 double gemm2_pd_us(const GemmDims& d, int nb) {
   const int splitk = gemm2_pd_split(d, nb);
-  const PdShape s = pd2_shape(d, nb, splitk);
+  const PdShape s = pd2_shape(d, nb);
   const int mi = pd_mi(nb), kb = pd_kb(mi, s.nj, s.kg, 64);
   const long blocks = (long)pd_mt(nb) * ceil_div((long)d.nv * d.nc, s.columns()) * splitk;
   return (6.0 + pd_us(blocks, s, mi, kb, split_chunk(d.nrp, splitk, kUnitPd) / kb, 0.035,
@@ -541,10 +539,8 @@ void gemm2_pd(const GemmDims& d, int nb, int splitk, const double* psi_v_t,
     gemm2_pd_kernel<MIV, NJV, KGV><<<pd_grid((long)mt * nt * splitk), NT, 0, st>>>(        \
         d, nvc, nb, mt, nt, splitk, kchunk, psi_v_t, psi_c_t, vpot, ypart);                \
   } while (0)
-  const PdShape s = pd2_shape(d, nb, splitk);
-  if (s.nj == 2) {
-    GWL_PD_MI(2, 1)
-  } else if (s.kg == 1) {
+  const PdShape s = pd2_shape(d, nb);
+  if (s.kg == 1) {
     GWL_PD_MI(1, 1)
   } else if (s.kg == 2) {
     GWL_PD_MI(1, 2)
