@@ -1,6 +1,8 @@
 // Hartree solve in three passes of in-place transforms (see fft_poisson.hip
 // for the solve, its packing of two real fields into one complex field and the
-// y-major spectrum X[ky][x][kz] between the passes):
+// y-major spectrum X[ky][x][kz] between the passes), for edges of 2 to 81 points
+// and 96, 108, 128 and 144 whose yz planes fit in 160 KB: in FP32 all but 144 x
+// 144, in FP64 up to 96 x 96 (128 x 72, 144 x 64):
 //   forward plane pass (fixed x): z lines, then y lines
 //   x pass (fixed ky):            x lines, v(G)/N, x lines back
 //   inverse plane pass:           y lines, then z lines
@@ -9,7 +11,8 @@
 // over n = j + R2 a (a < R1), then R2-point ones over j that give the
 // frequencies k = r + R1 k2 (Cooley and Tukey; a step is one or two of the
 // radix-2, 3, 4 and 8 stages of fft_poisson.hip, with the same twiddles in the
-// same order, so every value is bitwise that of the stage-by-stage transform).
+// same order, so values equal those of the stage-by-stage transform but for
+// which of their products are rounded by themselves).
 // Both steps write where they read (slot j + R2 r, then k2 + R2 r): one barrier
 // each, no second buffer, no limit on butterflies per thread; the order of the
 // slots is left to the addresses of whoever reads them next.  The inverse is

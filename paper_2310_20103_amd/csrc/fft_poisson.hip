@@ -12,7 +12,7 @@
 //   x forward, multiply by v(G)/N, x inverse -> yz inverse (+ unpack),
 // with the spectrum in between stored y-major (X[ky][x][kz]) so that the x
 // pass reads and writes contiguous (x, kz) slabs;
-// otherwise (FP64 planes above 160 KB) five passes of batched 1-D transforms:
+// otherwise (planes too large for either) five passes of batched 1-D transforms:
 //   z forward (+ pack) -> y forward -> x (as above) -> y inverse -> z inverse.
 // The 1-D transforms are mixed-radix (2, 3, 4, 8) Stockham autosort passes
 // with ping-pong LDS buffers (Govindaraju et al., SC'08 formulation); the
