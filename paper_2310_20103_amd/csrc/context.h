@@ -230,6 +230,8 @@ struct gwl_ctx {
   // the other precision's bytes.
   DevBuf<double> u64;          // [cap][NVp][NCp]
   DevBuf<double> u64c;         // [cap][N_v N_c] operand of the pair-density GEMMs
+  bool pairs_fit = true;       // u64c is there
+  bool wide_splits = true;     // ypart has room for 64 splits of fewer than 32 slots
   DevBuf<f16_t> u16;           // [cap][NVp][NCp] FP16, scaled by u_scale
   DevBuf<unsigned char> rho;   // [nvt][cap][NRp] x 8 (fully written by the first GEMM)
   DevBuf<double> vpot64;       // [cap][NRp]
@@ -362,7 +364,7 @@ struct gwl_ctx {
   // 1,328 with up to 64 vectors slower than the row GEMMs alone were before the
   // pair form was there.
   bool pd(int nb, Gemms g = kBoth) const {
-    if (fp64_kernel != 1) return false;
+    if (fp64_kernel != 1 || !pairs_fit) return false;
     const GemmDims& d = dims_of(g);
     if (form.nb == nb && form.gemms == g && form.nrp == d.nrp && form.isdf == isdf_on)
       return form.pair;
@@ -488,7 +490,7 @@ struct gwl_ctx {
   }
   // Splits the partial sums' buffer has room for, whatever the batch it was
   // sized for: small batches may take more (they have few tiles).
-  static int max_splitk(int nb) { return nb < 32 ? 64 : 32; }
+  int max_splitk(int nb) const { return nb < 32 && wide_splits ? 64 : 32; }
   static size_t split_rows(int cap) { return std::max((size_t)32 * cap, (size_t)64 * std::min(cap, 31)); }
 
   void ensure_work(int nb, int Lrows, bool need_basis) {
@@ -507,7 +509,6 @@ struct gwl_ctx {
       ta.ensure((size_t)nb * nvc, false);
       tb.ensure((size_t)nb * nvc, false);
       u64.ensure((size_t)nb * nvpc, false);
-      u64c.ensure(gemm_pd_u_size(nb, nvc), false);
       u16.ensure((size_t)alloc_rows_u(nb, gd.nvp) * gd.ncp, false);
       rho.ensure((size_t)nvt_max() * nb * gd.nrp * 8, false);
       vpot64.ensure((size_t)nb * gd.nrp, false);
@@ -516,7 +517,6 @@ struct gwl_ctx {
       xmax32.ensure((size_t)alloc_rows_v(nb, gd.nvp), false);
       vexp32.ensure((size_t)alloc_rows_v(nb, gd.nvp), false);
       fftx.ensure((size_t)((nb + 1) / 2) * nr * 16, false);
-      ypart.ensure(split_rows(nb) * nvpc * 8, false);
       s_pair.ensure(nb, false);
       s_k.ensure(nb, false);
       s_len.ensure(nb, false);
@@ -530,6 +530,22 @@ struct gwl_ctx {
       rw_n0.ensure(nb, false);
       rw_part.ensure((size_t)nb * reorth_part_len(nvc), false);
       rw_skip.ensure(nb, false);
+      // what a product can do without comes last
+      pairs_fit = wide_splits = true;
+      try {
+        ypart.ensure(split_rows(nb) * nvpc * 8, false);
+      } catch (const Error& e) {
+        if (e.code != GWL_ENOMEM) throw;
+        wide_splits = false;
+        ypart.ensure((size_t)32 * nb * nvpc * 8, false);
+      }
+      try {
+        u64c.ensure(gemm_pd_u_size(nb, nvc), false);
+      } catch (const Error& e) {
+        if (e.code != GWL_ENOMEM) throw;
+        pairs_fit = false;
+      }
+      form.nb = -1;
       GWL_HIP(hipDeviceSynchronize());  // one wait for all the fills
       cap = nb;
     }
